@@ -1,0 +1,407 @@
+"""Performance cases of the Hidden Decoding hot path on one GPU.
+
+Each case is one call (or one forward and its backward) of the library's public entry
+points at sizes a training run or a serving loop gives them.  ``listed()`` names the
+standing cases, ``draw(rng)`` gives further ones of the same ranges; ``prepare`` makes the
+inputs and the buffers such a program keeps, ``run`` makes one pass, ``work`` counts the
+bytes and flops a pass cannot do without, ``tolerance`` says how far another correct
+implementation at the same precision may be off, and ``exact`` gives the same outputs in
+64-bit floating point from plain torch.
+
+Kinds of case (key ``kind``):
+  train    one attention layer, forward and backward (masks intra, mix, local);
+  final    one final-stream (KV-mirror) layer, forward and backward;
+  prefill  one attention layer, forward only;
+  decode   one parallel-stream decode step over cached keys and values;
+  ends     the two ends of the stream layout in a training step: the token expansion, the
+           gather of the loss input and that gather's adjoint;
+  embed    the gradient of the expansion with respect to the embedding tables.
+"""
+import math
+
+import torch
+
+import paper_2607_08186_amd as hd
+
+MODES = {"intra": hd.HD_SFA_INTRA, "mix": hd.HD_SFA_MIX, "local": hd.HD_SFA_LOCAL}
+DTYPES = {"bf16": torch.bfloat16, "f32": torch.float32}
+VOCAB = 151936
+
+
+# ------------------------------------------------------------------ the cases
+
+def attention(kind, mode, B, L, n, Hq, Hkv, D, *, dtype="bf16", window=0, workspace="one_pass",
+              name=None):
+    c = dict(kind=kind, mode=mode, B=B, L=L, n=n, Hq=Hq, Hkv=Hkv, D=D, dtype=dtype, window=window)
+    if kind != "prefill":
+        c["workspace"] = workspace
+    return dict(c, name=name) if name else c
+
+
+def decode(mode, B, ctx, n, Hq, Hkv, D, *, ragged, window=0, name=None):
+    c = dict(kind="decode", mode=mode, B=B, ctx=ctx, n=n, Hq=Hq, Hkv=Hkv, D=D, ragged=ragged,
+             window=window)
+    return dict(c, name=name) if name else c
+
+
+def rows(kind, B, L, n, Dm, *, dtype="bf16", vocab=VOCAB, name=None):
+    c = dict(kind=kind, B=B, L=L, n=n, Dm=Dm, dtype=dtype, vocab=vocab)
+    return dict(c, name=name) if name else c
+
+
+def listed():
+    return [
+        # A layer in full precision, as gradient checks and small accuracy-first runs use it.
+        attention("train", "mix", 1, 256, 2, 8, 2, 64, dtype="f32", name="f32_layer"),
+        # The base model's own layer before any expansion (n = 1): a small training layer.
+        attention("train", "mix", 2, 2048, 1, 32, 8, 128, name="train_n1"),
+        # The layer that makes up most of the 36-layer stack.
+        attention("train", "intra", 1, 4096, 4, 32, 8, 128, name="train_intra"),
+        # The stack's cross-stream layers; the largest case.
+        attention("train", "mix", 1, 4096, 4, 32, 8, 128, name="train_mix"),
+        # The same with the base model's sliding window (1024 tokens at n = 4).
+        attention("train", "local", 1, 4096, 4, 32, 8, 128, window=4096, name="train_local"),
+        # A mirrored layer: queries of the final stream only.
+        attention("final", "mix", 1, 4096, 4, 32, 8, 128, name="train_final"),
+        # A prompt of no particular length before decoding.
+        attention("prefill", "mix", 1, 1531, 4, 32, 8, 128, name="prefill_ragged"),
+        # A serving step over a full batch: every cached row is read once.
+        decode("mix", 16, 4095, 4, 32, 8, 128, ragged=False, name="decode_batch"),
+        # One sequence with a short context, own-stream layer: the smallest call.
+        decode("intra", 1, 777, 4, 32, 8, 128, ragged=False, name="decode_single"),
+        # Expansion through the stack's tables, and the loss input with its adjoint.
+        rows("ends", 1, 4096, 4, 4096, name="stream_ends"),
+        # Table gradient of one stack step.
+        rows("embed", 1, 4096, 4, 4096, name="embed_grad"),
+        # Table gradient of a larger batch.
+        rows("embed", 8, 4096, 4, 2048, name="embed_grad_batch"),
+    ]
+
+
+HEADS = ((32, 8), (32, 8), (16, 4), (8, 2), (8, 8), (64, 8), (12, 4))
+
+
+def log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """One more case of the listed ranges, at most as costly as the largest listed one."""
+    most = max(_cost(c) for c in listed())
+    while True:
+        c = _draw(rng)
+        if _cost(c) <= most and c["n"] * c.get("L", 0) <= 32768:
+            return c
+
+
+def _cost(c):
+    # about the time of a pass: bytes at 5 TB/s, bf16 flops at 900 TFLOP/s, and fp32 layers
+    # (vector units, one row per lane) at a two-hundredth of that
+    w = work(c)
+    return max(w["bytes"] / 5e12, w["flops"] / (4.5e12 if c.get("dtype") == "f32" and "Hq" in c else 9e14))
+
+
+def _draw(rng):
+    kind = rng.choice(("train", "train", "train", "f32", "final", "prefill", "decode", "decode",
+                       "ends", "embed"))
+    n = rng.choice((1, 2, 3, 4, 4, 8))
+    Hq, Hkv = rng.choice(HEADS)
+    D = rng.choice((128, 128, 64, 32))
+    B = rng.choice((1, 1, 2, 3))
+    if kind == "f32":
+        mode = rng.choice(("intra", "mix", "local"))
+        Hq, Hkv = rng.choice(((2, 1), (8, 2), (8, 8), (12, 4)))
+        L = log_int(rng, 64, 512)
+        window = log_int(rng, 16, n * L) if mode == "local" else 0
+        return attention("train", mode, B, L, n, Hq, Hkv, D, dtype="f32", window=window)
+    if kind in ("train", "prefill"):
+        mode = rng.choice(("intra", "intra", "mix", "local"))
+        L = log_int(rng, 200, 8192)
+        window = log_int(rng, 128, n * L) if mode == "local" else 0
+        ws = rng.choice(("one_pass",) * 5 + ("min",)) if kind == "train" else None
+        return attention(kind, mode, B, L, n, Hq, Hkv, D, window=window, workspace=ws)
+    if kind == "final":
+        mode = rng.choice(("mix", "local"))
+        L = log_int(rng, 200, 8192)
+        window = log_int(rng, 128, n * L) if mode == "local" else 0
+        return attention("final", mode, B, L, n, Hq, Hkv, D, window=window)
+    if kind == "decode":
+        mode = rng.choice(("intra", "mix", "mix", "local"))
+        B, ctx = log_int(rng, 1, 32), log_int(rng, 100, 8192)
+        window = log_int(rng, 128, n * ctx) if mode == "local" else 0
+        return decode(mode, B, ctx, n, Hq, Hkv, D, ragged=rng.random() < 0.5, window=window)
+    dtype = rng.choice(("bf16", "bf16", "bf16", "f32"))
+    Dm = rng.choice((512, 1000, 1024, 2048, 2050, 4096))
+    B = rng.choice((1, 1, 2, 8)) if kind == "embed" else B
+    return rows(kind, B, log_int(rng, 50, 8192), n, Dm, dtype=dtype, vocab=rng.choice((VOCAB, 32000)))
+
+
+# ------------------------------------------------------------------ inputs
+
+def _normal(gen, shape, std, dtype):
+    x = torch.empty(shape, dtype=dtype, device="cuda")
+    return x.normal_(0.0, std, generator=gen)
+
+
+def _token_ids(gen, B, L, vocab):
+    """Token ids with the frequencies of running text: rank r has weight 1 / (r + 2.7)."""
+    cdf = torch.cumsum(1.0 / (torch.arange(vocab, device="cuda", dtype=torch.float64) + 2.7), 0)
+    u = torch.rand((B, L), device="cuda", dtype=torch.float64, generator=gen) * cdf[-1]
+    return torch.searchsorted(cdf, u).clamp_(max=vocab - 1).to(torch.int32)
+
+
+def _contexts(c):
+    """Cached tokens of each sequence: all alike, or between 9/16 and all of ``ctx``."""
+    return [c["ctx"] - (c["ctx"] * ((5 * b) % 8) // 16 if c["ragged"] else 0) for b in range(c["B"])]
+
+
+def _inputs(c, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    B, n = c["B"], c["n"]
+    if c["kind"] in ("ends", "embed"):
+        L, Dm, dt = c["L"], c["Dm"], DTYPES[c["dtype"]]
+        s = dict(ids=_token_ids(gen, B, L, c["vocab"]))
+        if c["kind"] == "ends":
+            s["tables"] = _normal(gen, (n, c["vocab"], Dm), 0.02, dt)
+            s["h"] = _normal(gen, (B, n * L, Dm), 1.0, dt)
+            s["dfinal"] = _normal(gen, (B, L, Dm), 1.0, dt)
+        else:
+            s["dout"] = _normal(gen, (B, n * L, Dm), 1.0, dt)
+        return s
+    Hq, Hkv, D, std = c["Hq"], c["Hkv"], c["D"], 1.0 / math.sqrt(2.0)
+    dt = DTYPES[c.get("dtype", "bf16")]
+    if c["kind"] == "decode":
+        Lcap = c["ctx"] + 1
+        return dict(q=_normal(gen, (B, n, Hq, D), std, dt),
+                    k=_normal(gen, (B, n * Lcap, Hkv, D), std, dt),
+                    v=_normal(gen, (B, n * Lcap, Hkv, D), std, dt),
+                    ctx=torch.tensor(_contexts(c), dtype=torch.int32, device="cuda"))
+    L = c["L"]
+    qrows = L if c["kind"] == "final" else n * L
+    s = dict(q=_normal(gen, (B, qrows, Hq, D), std, dt),
+             k=_normal(gen, (B, n * L, Hkv, D), std, dt),
+             v=_normal(gen, (B, n * L, Hkv, D), std, dt))
+    if c["kind"] != "prefill":
+        s["dO"] = _normal(gen, (B, qrows, Hq, D), 1.0, dt)
+    return s
+
+
+def _workspace_bytes(c):
+    dt = hd.HD_DTYPE_F32 if c["dtype"] == "f32" else hd.HD_DTYPE_BF16
+    a = [c[x] for x in ("B", "L", "n", "Hq", "Hkv", "D")]
+    least = c["workspace"] == "min"
+    if c["kind"] == "final":
+        f = hd.hd_sfa_bwd_final_min_workspace_bytes if least else hd.hd_sfa_bwd_final_workspace_bytes
+        return f(*a, c["window"], dt)
+    if c["mode"] == "local":
+        f = hd.hd_sfa_bwd_local_min_workspace_bytes if least else hd.hd_sfa_bwd_local_workspace_bytes
+        return f(*a, c["window"], dt)
+    f = hd.hd_sfa_bwd_min_workspace_bytes if least else hd.hd_sfa_bwd_workspace_bytes
+    return f(*a, MODES[c["mode"]], dt)
+
+
+def prepare(case, seed):
+    s = _inputs(case, seed)
+    s["case"] = case
+    kind = case["kind"]
+    if kind in ("train", "final"):
+        s["workspace"] = torch.empty(_workspace_bytes(case), dtype=torch.uint8, device="cuda")
+    elif kind == "decode":
+        need = hd.hd_sfa_decode_workspace_bytes(case["B"], case["ctx"] + 1, case["n"], case["Hq"],
+                                                case["Hkv"], case["D"], MODES[case["mode"]],
+                                                case["window"], case["ctx"])
+        s["workspace"] = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+    elif kind == "embed":
+        # the sparse gradient's buffers, kept from step to step (rows past the distinct ids
+        # are not written)
+        B, L, n, Dm = (case[x] for x in ("B", "L", "n", "Dm"))
+        s["uniq"] = torch.zeros(B * L, dtype=torch.int32, device="cuda")
+        s["drows"] = torch.zeros((n, B * L, Dm), dtype=torch.float32, device="cuda")
+        s["num"] = torch.zeros(1, dtype=torch.int32, device="cuda")
+        s["workspace"] = torch.empty(hd.hd_expand_embed_bwd_workspace_bytes(B, L),
+                                     dtype=torch.uint8, device="cuda")
+    return s
+
+
+# ------------------------------------------------------------------ one pass
+
+def run(state):
+    s, c = state, state["case"]
+    kind, n = c["kind"], c["n"]
+    if kind == "ends":
+        return dict(x=hd.expand_embed(s["ids"], s["tables"]),
+                    final=hd.final_stream_gather(s["h"], n),
+                    dh=hd.final_stream_gather_backward(s["dfinal"], n))
+    if kind == "embed":
+        hd.hd_expand_embed_bwd(s["ids"], s["dout"], c["B"], c["L"], n, c["vocab"], c["Dm"], s["uniq"],
+                               s["drows"], s["num"], s["workspace"], s["workspace"].numel())
+        return dict(uniq=s["uniq"], drows=s["drows"], num=s["num"])
+    scale, mode = c["D"] ** -0.5, MODES[c["mode"]]
+    if kind == "decode":
+        o, lse = hd.sfa_decode(s["q"], s["k"], s["v"], s["ctx"], max_ctx=c["ctx"], mode=mode,
+                               scale=scale, window=c["window"], workspace=s["workspace"])
+        return dict(o=o, lse=lse)
+    if kind == "final":
+        o, lse = hd.sfa_final_forward(s["q"], s["k"], s["v"], n=n, scale=scale, window=c["window"])
+        dq, dk, dv = hd.sfa_final_backward(s["q"], s["k"], s["v"], o, lse, s["dO"], n=n, scale=scale,
+                                           window=c["window"], workspace=s["workspace"])
+        return dict(o=o, lse=lse, dq=dq, dk=dk, dv=dv)
+    window = c["window"] if c["mode"] == "local" else None
+    o, lse = hd.sfa_forward(s["q"], s["k"], s["v"], n=n, mode=mode, scale=scale, window=window)
+    if kind == "prefill":
+        return dict(o=o, lse=lse)
+    dq, dk, dv = hd.sfa_backward(s["q"], s["k"], s["v"], o, lse, s["dO"], n=n, mode=mode, scale=scale,
+                                 window=window, workspace=s["workspace"])
+    return dict(o=o, lse=lse, dq=dq, dk=dk, dv=dv)
+
+
+# ------------------------------------------------------------------ work
+
+def _pairs(c):
+    """Visible (query, key) pairs over batch and query heads."""
+    B, L, n, Hq = c["B"], c["L"], c["n"], c["Hq"]
+    if c["mode"] == "intra":
+        return B * Hq * n * L * (L + 1) // 2
+    w = c["window"] if c["mode"] == "local" else n * L
+    if c["kind"] == "final":
+        return B * Hq * sum(min((t + 1) * n, w) for t in range(L))
+    w = min(w, n * L)
+    return B * Hq * (w * (w + 1) // 2 + (n * L - w) * w)
+
+
+def _distinct(vocab, M):
+    """Expected number of distinct ids among M draws of ``_token_ids``."""
+    w = 1.0 / (torch.arange(vocab, dtype=torch.float64) + 2.7)
+    return float((1.0 - torch.pow(1.0 - w / w.sum(), M)).sum())
+
+
+def work(case):
+    c = case
+    B, n = c["B"], c["n"]
+    if c["kind"] in ("ends", "embed"):
+        L, e = c["L"], 4 if c["dtype"] == "f32" else 2
+        row, M = c["Dm"] * e, B * L
+        if c["kind"] == "ends":
+            # expansion: n rows read and written per token; gather: one and one; adjoint: one
+            # read, n written
+            return dict(bytes=M * (4 + row * (2 * n + 2 + 1 + n)), flops=0)
+        U = _distinct(c["vocab"], M)
+        return dict(bytes=M * 4 + M * n * row + U * 4 + n * U * c["Dm"] * 4, flops=M * n * c["Dm"])
+    Hq, Hkv, D = c["Hq"], c["Hkv"], c["D"]
+    if c["kind"] == "decode":
+        kvrows = pairs = 0
+        for ctx in _contexts(c):
+            if c["mode"] == "local":
+                w = c["window"]
+                kvrows += min((ctx + 1) * n, w + n - 1)
+                pairs += sum(min(ctx * n + s + 1, w) for s in range(n))
+            else:
+                kvrows += (ctx + 1) * n
+                pairs += n * (ctx + 1) if c["mode"] == "intra" else sum(ctx * n + s + 1 for s in range(n))
+        return dict(bytes=2 * kvrows * Hkv * D * 2 + 2 * B * n * Hq * D * 2 + B * n * Hq * 4,
+                    flops=4 * D * Hq * pairs)
+    e = 4 if c["dtype"] == "f32" else 2
+    qrows = B * (c["L"] if c["kind"] == "final" else n * c["L"])
+    krows = B * n * c["L"]
+    qb, kb, lb = qrows * Hq * D * e, krows * Hkv * D * e, qrows * Hq * 4
+    if c["kind"] == "prefill":
+        return dict(bytes=2 * qb + 2 * kb + lb, flops=4 * D * _pairs(c))
+    # q, dO read; o, dq written; k, v read; dk, dv written; lse written
+    return dict(bytes=4 * qb + 4 * kb + lb, flops=14 * D * _pairs(c))
+
+
+def tolerance(case):
+    """Relative 2-norm bounds, about four times the distance measured between the kernels
+    and ``exact``: bf16 attention 1.9e-3 to 2.5e-3 (bf16 weights, dS and outputs), fp32
+    attention up to 9.2e-7 at the listed size (allowed: 1e-5, as the sums get longer), fp32
+    table gradients up to 1.5e-8 over runs of up to 900 rows.  Copies are exact."""
+    if case["kind"] == "ends":
+        return "exact"
+    if case["kind"] == "embed":
+        return {"rel": 1e-7, "max": 1e-5}
+    if case.get("dtype") == "f32":
+        return {"rel": 1e-5, "max": 1e-3}
+    return {"rel": 1e-2, "max": 0.25}
+
+
+# ------------------------------------------------------------------ the same in 64 bits
+
+def _softmax_rows(q, k, v, qpos, kpos, window, scale):
+    """(o, lse, P) of fp64 rows q at positions qpos against k, v at kpos."""
+    S = (q @ k.t()).mul_(scale)
+    d = qpos[:, None] - kpos[None, :]
+    S.masked_fill_((d < 0) | (d >= window), -math.inf)
+    lse = torch.logsumexp(S, 1)
+    P = S.sub_(lse[:, None]).exp_()
+    return P @ v, lse, P
+
+
+def exact(case, seed):
+    c = case
+    s = _inputs(c, seed)
+    B, n = c["B"], c["n"]
+    dev, f64 = "cuda", torch.float64
+    if c["kind"] == "ends":
+        ids, L = s["ids"].long(), c["L"]
+        x = torch.stack([s["tables"][j][ids] for j in range(n)], 2).reshape(B, n * L, c["Dm"])
+        dh = torch.zeros((B, n * L, c["Dm"]), dtype=s["h"].dtype, device=dev)
+        dh[:, n - 1::n] = s["dfinal"]
+        return dict(x=x, final=s["h"][:, n - 1::n].contiguous(), dh=dh)
+    if c["kind"] == "embed":
+        L, Dm, M = c["L"], c["Dm"], B * c["L"]
+        uniq, inv = torch.unique(s["ids"].reshape(-1), sorted=True, return_inverse=True)
+        d = s["dout"].reshape(M, n, Dm)
+        drows = torch.zeros((n, M, Dm), dtype=f64, device=dev)
+        for j in range(n):
+            drows[j].index_add_(0, inv, d[:, j].to(f64))
+        ids = torch.zeros(M, dtype=torch.int32, device=dev)
+        ids[:uniq.numel()] = uniq
+        return dict(uniq=ids, drows=drows,
+                    num=torch.tensor([uniq.numel()], dtype=torch.int32, device=dev))
+    Hq, Hkv, D = c["Hq"], c["Hkv"], c["D"]
+    G, scale, huge = Hq // Hkv, D ** -0.5, 1 << 40
+    window = c["window"] if c["mode"] == "local" else huge
+    if c["kind"] == "decode":
+        o = torch.zeros((B, n, Hq, D), dtype=f64, device=dev)
+        lse = torch.zeros((B, Hq, n), dtype=f64, device=dev)
+        for b, ctx in enumerate(_contexts(c)):
+            N = (ctx + 1) * n
+            pos = torch.arange(N, device=dev)
+            for h in range(Hkv):
+                k, v = s["k"][b, :N, h].to(f64), s["v"][b, :N, h].to(f64)
+                for j in range(n):
+                    sel = slice(j, N, n) if c["mode"] == "intra" else slice(0, N)
+                    q = s["q"][b, j, h * G:(h + 1) * G].to(f64)
+                    qpos = torch.full((G,), ctx * n + j, device=dev)
+                    ob, lb, _ = _softmax_rows(q, k[sel], v[sel], qpos, pos[sel], window, scale)
+                    o[b, j, h * G:(h + 1) * G] = ob
+                    lse[b, h * G:(h + 1) * G, j] = lb
+        return dict(o=o, lse=lse)
+    N = n * c["L"]
+    back = c["kind"] != "prefill"
+    out = dict(o=torch.empty(s["q"].shape, dtype=f64, device=dev),
+               lse=torch.empty((B, Hq, s["q"].shape[1]), dtype=f64, device=dev))
+    if back:
+        out.update(dq=torch.empty(s["q"].shape, dtype=f64, device=dev),
+                   dk=torch.zeros(s["k"].shape, dtype=f64, device=dev),
+                   dv=torch.zeros(s["v"].shape, dtype=f64, device=dev))
+    pos = torch.arange(N, device=dev)
+    streams = range(n) if c["mode"] == "intra" else (0,)
+    step = n if c["mode"] == "intra" else 1
+    for b in range(B):
+        for h in range(Hq):
+            for j in streams:
+                kk = slice(j, N, step)
+                qq = slice(None) if c["kind"] == "final" else kk
+                qpos = pos[n - 1::n] if c["kind"] == "final" else pos[kk]
+                q = s["q"][b, qq, h].to(f64)
+                k, v = s["k"][b, kk, h // G].to(f64), s["v"][b, kk, h // G].to(f64)
+                o, lse, P = _softmax_rows(q, k, v, qpos, pos[kk], window, scale)
+                out["o"][b, qq, h], out["lse"][b, h, qq] = o, lse
+                if back:
+                    dO = s["dO"][b, qq, h].to(f64)
+                    out["dv"][b, kk, h // G] += P.t() @ dO
+                    dS = (dO @ v.t()).sub_((dO * o).sum(1, keepdim=True)).mul_(P).mul_(scale)
+                    out["dq"][b, qq, h] = dS @ k
+                    out["dk"][b, kk, h // G] += dS.t() @ q
+    return out
