@@ -314,11 +314,12 @@ def tolerance(case):
     """Relative 2-norm bounds, about four times the distance measured between the kernels
     and ``exact``: bf16 attention 1.9e-3 to 2.5e-3 (bf16 weights, dS and outputs), fp32
     attention up to 9.2e-7 at the listed size (allowed: 1e-5, as the sums get longer), fp32
-    table gradients up to 1.5e-8 over runs of up to 900 rows.  Copies are exact."""
+    table gradients up to 1.5e-8 over bf16 rows (allowed: 1e-6, the rounding of fp32 sums
+    of fp32 rows over runs of hundreds).  Copies are exact."""
     if case["kind"] == "ends":
         return "exact"
     if case["kind"] == "embed":
-        return {"rel": 1e-7, "max": 1e-5}
+        return {"rel": 1e-6, "max": 1e-4}
     if case.get("dtype") == "f32":
         return {"rel": 1e-5, "max": 1e-3}
     return {"rel": 1e-2, "max": 0.25}
