@@ -2,86 +2,388 @@
 // preprocess, which forms Delta and the base-2 lse of every query row; the bf16 path
 // forms its row statistics in a kernel of its own before the dK/dV pass).
 //
-// The fp32 kernels serve small, accuracy-first workloads: one lane owns one query row
-// (forward, dQ) or one key row (dK/dV), tiles of the other operand are staged in LDS
-// and read as broadcasts.  Arithmetic is plain fp32 FMA with an fp32 online softmax.
-// Same problem decomposition as the bf16 path (see SfaGeom).
+// All products run on the matrix cores in fp32 (16x16x4 MFMA: fp32 operands, fp32
+// multiply-add), softmax in fp32; same problem decomposition as the bf16 path (see
+// SfaGeom).  These layers are small (gradient checks, accuracy-first runs), so what
+// bounds them is the length of the longest workgroup's serial sweep and how many CUs
+// have work.  Hence:
+//   tiles of 16 rows: a workgroup owns 16 or 32 query rows (forward, dQ) or keys (dK/dV)
+//     of one problem, and its four waves take every fourth step of the sweep over the
+//     other operand, each with its own accumulators, added in LDS in a fixed order at
+//     the end (the forward's after scaling to the waves' common row maximum);
+//   no LDS and no barrier inside a sweep: operands go from memory (L1/L2) to registers in
+//     the layout the MFMA takes, the next step's loads issued as soon as the registers of
+//     the current one are free;
+//   dK/dV and dQ in one launch, the longer dK/dV workgroups first, so that both fill the
+//     chip together.
+//
+// 16x16x4 MFMA layout: lane l supplies row (A) or column (B) l % 16 at k-slot l / 16; result
+// register r of lane l is row 4 (l / 16) + r, column l % 16.  Two operand forms follow:
+//   row form    (k-slots run along the head dim): lane (i, g) = (l % 16, l / 16) holds
+//     dims 16c + 4g .. + 3 of row i for every c, 16 bytes a load; MFMA (c, e) takes
+//     element e of load c on both sides;
+//   column form (k-slots run along the rows): MFMA r takes row 4g + r, the rows that result
+//     register r of a score tile holds, so P and dS feed the next product from
+//     registers.  Lane i loads W = min(4, D/16) consecutive dims per block group, which
+//     serve W MFMAs: output row i of block b is dim (b / W) 16 W + i W + b % W.
 #include "hd_device.h"
 
 namespace hd {
 
 namespace {
 
-constexpr int kRows = 64;  // rows per workgroup (one wave)
+constexpr int kT = 16;      // rows or keys per MFMA tile
+constexpr int kWaves = 4;   // waves per workgroup, splitting the sweep
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <int D>
-__global__ __launch_bounds__(64) void sfa_fwd_f32_kernel(const float *__restrict__ q,
-                                                         const float *__restrict__ k,
-                                                         const float *__restrict__ v,
-                                                         float *__restrict__ o,
-                                                         float *__restrict__ lse, SfaGeom g)
+__device__ inline f32x4 mfma16f(float a, float b, f32x4 c)
 {
-    __shared__ float sk[kRows][D];
-    __shared__ float sv[kRows][D];
-    const int ntiles = (g.len + kRows - 1) / kRows;
-    const int nprob = g.B * g.Hq * g.streams;
-    int prob, tile;
-    decode_tile(blockIdx.x, nprob, ntiles, prob, tile);
-    const int s = prob % g.streams, hq = (prob / g.streams) % g.Hq;
-    const int b = prob / (g.streams * g.Hq), hk = hq / g.G;
-    const int tid = threadIdx.x, row = tile * kRows + tid;
-    const size_t qs = (size_t)g.rowmul * g.Hq * D, ks = (size_t)g.rowmul * g.Hkv * D;
-    const float *qb = q + (size_t)b * g.N * g.Hq * D + (size_t)(s * g.Hq + hq) * D;
-    const float *kb = k + (size_t)b * g.N * g.Hkv * D + (size_t)(s * g.Hkv + hk) * D;
-    const float *vb = v + (size_t)b * g.N * g.Hkv * D + (size_t)(s * g.Hkv + hk) * D;
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
-    float qv[D], acc[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        qv[d] = row < g.len ? qb[row * qs + d] : 0.f;
-        acc[d] = 0.f;
+// max / sum over the four lanes l % 16 + 16 g (g = 0 .. 3) that hold one column
+__device__ inline float max_groups(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return max_xor32(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float sum_groups(float v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return sum_xor32(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+__device__ inline bool not_finite(float x) { return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u; }
+
+// Rows of one problem inside a batch slice: row i at byte base + i * stride; rows outside
+// [0, len) read zeros.
+struct Rows {
+    rsrc_t rs;
+    uint32_t base, stride;
+    int len;
+    __device__ inline uint32_t off(int row) const
+    {
+        return row >= 0 && row < len ? base + (uint32_t)row * stride : kOob;
     }
-    float m = -INFINITY, l = 0.f;
-    const int kend = min(g.len, tile * kRows + kRows);
-    // first key any row of the tile sees (local layers: window)
-    const int kbeg = max(0, tile * kRows - g.window + 1) / kRows * kRows;
-    for (int j0 = kbeg; j0 < kend; j0 += kRows) {
-        __syncthreads();
-        const int key = j0 + tid;
+};
+
+template <int D>
+struct Ops {
+    static constexpr int C = D / 16;             // row form: 16-byte loads per row and lane
+    static constexpr int NB = D / 16;            // column form: 16-dim output blocks
+    static constexpr int W = NB < 4 ? NB : 4;    // dims per lane and load
+    static_assert(W == 4 || W == 2, "16- or 8-byte column loads");
+
+    // element 4c + e: dim 16c + 4g + e of row row0 + i
+    __device__ static inline void row_form(const Rows &m, int row0, int lane, f32x4 (&a)[C])
+    {
+        const uint32_t off = m.off(row0 + (lane & 15)) + (lane >> 4) * 16;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            sk[tid][d] = key < g.len ? kb[key * ks + d] : 0.f;
-            sv[tid][d] = key < g.len ? vb[key * ks + d] : 0.f;
-        }
-        __syncthreads();
-        if (row >= g.len) continue;
-        const int jn = min(kRows, row - j0 + 1);  // causal: keys j0 .. row
-        for (int jj = max(0, row - g.window + 1 - j0); jj < jn; ++jj) {
-            float dot = 0.f;
+        for (int c = 0; c < C; ++c) a[c] = __builtin_bit_cast(f32x4, ld16(m.rs, off + c * 64));
+    }
+    // a[r][b]: row row0 + 4g + r, dim of output row i in block b
+    __device__ static inline void col_form(const Rows &m, int row0, int lane, float (&a)[4][NB])
+    {
 #pragma unroll
-            for (int d = 0; d < D; ++d) dot = __builtin_fmaf(qv[d], sk[jj][d], dot);
-            const float x = dot * g.scale_log2;
-            if (x > m) {
-                const float alpha = exp2f(m - x);
-                l *= alpha;
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t off = m.off(row0 + 4 * (lane >> 4) + r) + (lane & 15) * (W * 4);
 #pragma unroll
-                for (int d = 0; d < D; ++d) acc[d] *= alpha;
-                m = x;
+            for (int j = 0; j < NB / W; ++j) {
+                if constexpr (W == 4) {
+                    const f32x4 x = __builtin_bit_cast(f32x4, ld16(m.rs, off + j * (16 * W * 4)));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a[r][j * W + e] = x[e];
+                } else {
+                    const auto x = __builtin_amdgcn_raw_buffer_load_b64(m.rs, off, 0, 0);
+                    a[r][0] = __uint_as_float(x[0]);
+                    a[r][1] = __uint_as_float(x[1]);
+                }
             }
-            const float p = exp2f(x - m);
-            l += p;
-#pragma unroll
-            for (int d = 0; d < D; ++d) acc[d] = __builtin_fmaf(p, sv[jj][d], acc[d]);
         }
     }
-    if (row < g.len) {
-        float *ob = o + (size_t)b * g.N * g.Hq * D + (size_t)(s * g.Hq + hq) * D + row * qs;
-        const float inv = 1.f / l;
+    // acc += A B over the head dim: rows of `a` against columns (rows) of `b`
+    __device__ static inline f32x4 dot(const f32x4 (&a)[C], const f32x4 (&b)[C], f32x4 acc)
+    {
 #pragma unroll
-        for (int d = 0; d < D; ++d) ob[d] = acc[d] * inv;
-        lse[((size_t)b * g.Hq + hq) * g.N + (size_t)row * g.rowmul + s] = (m + log2f(l)) * kLn2;
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma16f(a[c][e], b[c][e], acc);
+        return acc;
+    }
+    // acc^T += A^T w: the 16 rows of column form `a` weighted by w (register r: row 4g + r)
+    __device__ static inline void add(const float (&a)[4][NB], const f32x4 &w, f32x4 (&acc)[NB])
+    {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[b] = mfma16f(a[r][b], w[r], acc[b]);
+    }
+    // Same on a tile with masked pairs, whose weights are zero.  A masked pair must add
+    // nothing even where its row holds an infinity or a NaN (0 * inf is NaN), so such
+    // elements leave the MFMA and are added one by one for the visible pairs.  That path is
+    // rare: it works on accumulators parked in `park` (this wave's, NB * 256 floats of LDS) in
+    // plain loops, so that it costs the common one no registers.  vis(j): row row0 + j is
+    // visible to this lane's column.
+    template <typename Vis>
+    __device__ static inline void add_masked(const Rows &m, int row0, int lane, float *park,
+                                             const float (&a)[4][NB], const f32x4 &w, f32x4 (&acc)[NB], Vis vis)
+    {
+        bool bad = false;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) bad = bad || not_finite(a[r][b]);
+        if (__any(bad)) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) park[(b * 4 + q) * 64 + lane] = acc[b][q];
+#pragma unroll 1
+            for (int j = 0; j < kT; ++j) {
+                const int r = j & 3;
+                const float wj = r == 0 ? w[0] : r == 1 ? w[1] : r == 2 ? w[2] : w[3];
+                const float wr = __shfl(wj, (lane & 15) + 16 * (j >> 2));
+                const uint32_t off = m.off(row0 + j);
+                const bool v = vis(j);
+#pragma unroll 1
+                for (int x = 0; x < NB * 4; ++x) {
+                    const int b = x >> 2, q = x & 3;
+                    const uint32_t d = (b / W) * 16 * W + (4 * (lane >> 4) + q) * W + b % W;
+                    const float y = __uint_as_float(ld4(m.rs, off + d * 4));
+                    if (v && not_finite(y)) park[x * 64 + lane] = __builtin_fmaf(wr, y, park[x * 64 + lane]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[b][q] = park[(b * 4 + q) * 64 + lane];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[b] = mfma16f(not_finite(a[r][b]) ? 0.f : a[r][b], w[r], acc[b]);
+        } else {
+            add(a, w, acc);
+        }
+    }
+};
+
+// Writes elements r = wave of the 16-dim blocks of one column's accumulators, summed over
+// the waves: store(dim, four or two consecutive dims).
+template <int D, int NS>
+struct Merge {
+    // [wave][subtile][block][register][lane]
+    float v[kWaves][NS][Ops<D>::NB][4][64];
+    __device__ inline void put(int wave, int sub, int lane, const f32x4 (&acc)[Ops<D>::NB])
+    {
+#pragma unroll
+        for (int b = 0; b < Ops<D>::NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[wave][sub][b][r][lane] = acc[b][r];
+    }
+    // sum over the waves of block b, register r, each wave scaled by sc[wave]
+    __device__ inline float sum(int sub, int b, int r, int lane, const float (&sc)[kWaves]) const
+    {
+        float s = v[0][sub][b][r][lane] * sc[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) s = __builtin_fmaf(v[w][sub][b][r][lane], sc[w], s);
+        return s;
+    }
+    // register r of this lane's column, dims in order, scaled by f
+    template <typename Store>
+    __device__ inline void get(int sub, int r, int lane, const float (&sc)[kWaves], float f, Store store) const
+    {
+        constexpr int W = Ops<D>::W;
+#pragma unroll
+        for (int j = 0; j < Ops<D>::NB / W; ++j) {
+            float x[W];
+#pragma unroll
+            for (int e = 0; e < W; ++e) x[e] = sum(sub, j * W + e, r, lane, sc) * f;
+            store(j * 16 * W + (4 * (lane >> 4) + r) * W, x);
+        }
+    }
+};
+
+__device__ inline void store_dims(rsrc_t rs, uint32_t off, const float (&x)[4])
+{
+    st16(rs, off, u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])});
+}
+__device__ inline void store_dims(rsrc_t rs, uint32_t off, const float (&x)[2])
+{
+    st8(rs, off, u32x2{__float_as_uint(x[0]), __float_as_uint(x[1])});
+}
+
+// Work item -> (problem, tile) as decode_tile does, for item counts beyond 32 bits.
+__device__ inline void decode_item(int64_t id, int nprob, int ntiles, int &prob, int &tile)
+{
+    if ((nprob & 7) == 0) {
+        const int per = nprob >> 3;
+        const int64_t r = id >> 3;
+        tile = ntiles - 1 - (int)(r / per);
+        prob = (int)(id & 7) * per + (int)(r % per);
+    } else {
+        tile = ntiles - 1 - (int)(id / nprob);
+        prob = (int)(id % nprob);
+    }
+}
+
+// One (batch, query head[, stream]) or (batch, key head[, stream]) problem.
+struct Where {
+    int s, h, b;
+};
+__device__ inline Where where(const SfaGeom &g, int prob, int heads)
+{
+    return Where{prob % g.streams, prob / g.streams % heads, prob / (g.streams * heads)};
+}
+template <int D>
+__device__ inline Rows rows_of(const float *p, const SfaGeom &g, int b, int heads, int h, int s)
+{
+    const size_t slice = (size_t)g.N * heads * D;
+    return Rows{make_rsrc(p + b * slice, (uint32_t)(slice * 4)), (uint32_t)(s * heads + h) * D * 4,
+                (uint32_t)g.rowmul * heads * D * 4, g.len};
+}
+
+// Forward: NQ * 16 query rows; the waves take 32-key steps.  S^T = K Q^T puts a query's
+// scores in the four lanes of one column; O^T += V^T P^T.
+template <int D, int NQ>
+__global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_f32_kernel(const float *__restrict__ q,
+                                                                  const float *__restrict__ k,
+                                                                  const float *__restrict__ v,
+                                                                  float *__restrict__ o,
+                                                                  float *__restrict__ lse, SfaGeom g,
+                                                                  int64_t items)
+{
+    using P = Ops<D>;
+    constexpr int KS = 2, KT = KS * kT;  // keys per step
+    __shared__ Merge<D, NQ> mg;
+    __shared__ float sm[kWaves][NQ][16], sl[kWaves][NQ][16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, gr = lane >> 4;
+    const int ntiles = (g.len + NQ * kT - 1) / (NQ * kT);
+    for (int64_t id = blockIdx.x; id < items; id += gridDim.x) {
+        int prob, tile;
+        decode_item(id, g.B * g.Hq * g.streams, ntiles, prob, tile);
+        const Where at = where(g, prob, g.Hq);
+        const Rows rq = rows_of<D>(q, g, at.b, g.Hq, at.h, at.s);
+        const Rows rk = rows_of<D>(k, g, at.b, g.Hkv, at.h / g.G, at.s);
+        const Rows rv = rows_of<D>(v, g, at.b, g.Hkv, at.h / g.G, at.s);
+        const Rows ro = rows_of<D>(o, g, at.b, g.Hq, at.h, at.s);
+        const int q0 = tile * NQ * kT, qlast = q0 + NQ * kT - 1;
+
+        f32x4 qr[NQ][P::C], oacc[NQ][P::NB];
+        float m[NQ], l[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            P::row_form(rq, q0 + i * kT, lane, qr[i]);
+#pragma unroll
+            for (int b = 0; b < P::NB; ++b) oacc[i][b] = f32x4{};
+            m[i] = -INFINITY;
+            l[i] = 0.f;
+        }
+        // 32-key steps from the first key the window reaches to the diagonal
+        const int jf = max(0, q0 - g.window + 1) / KT;
+        const int je = (min(g.len, qlast + 1) + KT - 1) / KT;
+        f32x4 kr[KS][P::C];
+        float vc[KS][4][P::NB];
+        auto load_k = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < KS; ++t) P::row_form(rk, j * KT + t * kT, lane, kr[t]);
+        };
+        auto load_v = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < KS; ++t) P::col_form(rv, j * KT + t * kT, lane, vc[t]);
+        };
+        int j = jf + wave;
+        if (j < je) {
+            load_k(j);
+            load_v(j);
+        }
+        for (; j < je; j += kWaves) {
+            const int kb = j * KT;
+            f32x4 sc[KS][NQ];
+#pragma unroll
+            for (int t = 0; t < KS; ++t)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) sc[t][i] = P::dot(kr[t], qr[i], f32x4{});
+            if (j + kWaves < je) load_k(j + kWaves);
+            const bool masked = kb + KT - 1 > q0 || qlast - kb >= g.window;
+            auto visible = [&](int key, int i) __attribute__((always_inline)) {
+                const int d = q0 + i * kT + col - key;
+                return d >= 0 && d < g.window;
+            };
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int t = 0; t < KS; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float x = sc[t][i][r] * g.scale_log2;
+                        if (masked && !visible(kb + t * kT + 4 * gr + r, i)) x = -INFINITY;
+                        sc[t][i][r] = x;
+                        mx = fmaxf(mx, x);
+                    }
+                const float mn = fmaxf(m[i], max_groups(mx));
+                if (__any(mn > m[i])) {
+                    const float alpha = mn == m[i] ? 1.f : exp2f(m[i] - mn);
+                    m[i] = mn;
+                    l[i] *= alpha;
+#pragma unroll
+                    for (int b = 0; b < P::NB; ++b) oacc[i][b] *= alpha;
+                }
+                // a row without a visible key so far: weights exp2(-inf) = 0, not NaN
+                const float me = mn == -INFINITY ? 0.f : mn;
+#pragma unroll
+                for (int t = 0; t < KS; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        sc[t][i][r] = exp2f(sc[t][i][r] - me);
+                        l[i] += sc[t][i][r];
+                    }
+            }
+#pragma unroll
+            for (int t = 0; t < KS; ++t)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i)
+                    if (masked)
+                        P::add_masked(rv, kb + t * kT, lane, &mg.v[wave][0][0][0][0], vc[t], sc[t][i], oacc[i],
+                                      [&](int x) { return visible(kb + t * kT + x, i); });
+                    else
+                        P::add(vc[t], sc[t][i], oacc[i]);
+            if (j + kWaves < je) load_v(j + kWaves);
+        }
+        // merge the waves: the row's largest maximum, then each wave's share scaled to it
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            mg.put(wave, i, lane, oacc[i]);
+            const float lt = sum_groups(l[i]);
+            if (gr == 0) {
+                sm[wave][i][col] = m[i];
+                sl[wave][i][col] = lt;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int row = q0 + i * kT + col;
+            float mt = sm[0][i][col], lt = 0.f, scl[kWaves];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) mt = fmaxf(mt, sm[w][i][col]);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                // a wave without a step of this row has m = -inf, l = 0 and O = 0
+                scl[w] = sm[w][i][col] == -INFINITY && mt == -INFINITY ? 1.f : exp2f(sm[w][i][col] - mt);
+                lt = __builtin_fmaf(sl[w][i][col], scl[w], lt);
+            }
+            const uint32_t off = ro.off(row);
+            mg.get(i, wave, lane, scl, 1.f / lt,
+                   [&](int d, const float(&x)[P::W]) { store_dims(ro.rs, off + d * 4, x); });
+            if (wave == 0 && gr == 0 && row < g.len)
+                lse[((size_t)at.b * g.Hq + at.h) * g.N + (size_t)row * g.rowmul + at.s] =
+                    (mt + log2f(lt)) * kLn2;
+        }
+        __syncthreads();
     }
 }
 
@@ -118,158 +420,252 @@ __global__ __launch_bounds__(256) void bwd_preprocess_kernel(const float *__rest
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(64) void sfa_dq_f32_kernel(const float *__restrict__ q,
-                                                        const float *__restrict__ k,
-                                                        const float *__restrict__ v,
-                                                        const float *__restrict__ dO,
-                                                        const float *__restrict__ delta,
-                                                        const float *__restrict__ lse2,
-                                                        float *__restrict__ dq, SfaGeom g)
+// dK/dV of NS * 16 keys: the waves take (query tile, query head of the group) pairs.
+// S = Q K^T and dP = dO V^T put a key's pairs in the lanes of one column;
+// dV^T += dO^T P, dK^T += Q^T dS.
+template <int D, int NS>
+__device__ inline void dkdv_f32(const float *q, const float *k, const float *v, const float *dO,
+                                const float *delta, const float *lse2, float *dk, float *dv,
+                                const SfaGeom &g, int64_t id, Merge<D, NS> &mg)
 {
-    __shared__ float sk[kRows][D];
-    __shared__ float sv[kRows][D];
-    const int ntiles = (g.len + kRows - 1) / kRows;
-    const int nprob = g.B * g.Hq * g.streams;
+    using P = Ops<D>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, gr = lane >> 4;
+    const int ntiles = (g.len + NS * kT - 1) / (NS * kT);
     int prob, tile;
-    decode_tile(blockIdx.x, nprob, ntiles, prob, tile);
-    const int s = prob % g.streams, hq = (prob / g.streams) % g.Hq;
-    const int b = prob / (g.streams * g.Hq), hk = hq / g.G;
-    const int tid = threadIdx.x, row = tile * kRows + tid;
-    const size_t qs = (size_t)g.rowmul * g.Hq * D, ks = (size_t)g.rowmul * g.Hkv * D;
-    const size_t qoff = (size_t)b * g.N * g.Hq * D + (size_t)(s * g.Hq + hq) * D;
-    const float *kb = k + (size_t)b * g.N * g.Hkv * D + (size_t)(s * g.Hkv + hk) * D;
-    const float *vb = v + (size_t)b * g.N * g.Hkv * D + (size_t)(s * g.Hkv + hk) * D;
-    const size_t li = ((size_t)b * g.Hq + hq) * g.N + (size_t)row * g.rowmul + s;
+    decode_item(id, g.B * g.Hkv * g.streams, ntiles, prob, tile);
+    tile = ntiles - 1 - tile;  // early keys, which most queries see, first
+    const Where at = where(g, prob, g.Hkv);
+    const Rows rk = rows_of<D>(k, g, at.b, g.Hkv, at.h, at.s);
+    const Rows rv = rows_of<D>(v, g, at.b, g.Hkv, at.h, at.s);
+    const int k0 = tile * NS * kT, klast = k0 + NS * kT - 1;
 
-    float qv[D], dov[D], acc[D];
+    f32x4 kb[NS][P::C], vb[NS][P::C], ak[NS][P::NB], av[NS][P::NB];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        qv[d] = row < g.len ? q[qoff + row * qs + d] : 0.f;
-        dov[d] = row < g.len ? dO[qoff + row * qs + d] : 0.f;
-        acc[d] = 0.f;
+    for (int i = 0; i < NS; ++i) {
+        P::row_form(rk, k0 + i * kT, lane, kb[i]);
+        P::row_form(rv, k0 + i * kT, lane, vb[i]);
+#pragma unroll
+        for (int b = 0; b < P::NB; ++b) ak[i][b] = av[i][b] = f32x4{};
     }
-    const float l2 = row < g.len ? lse2[li] : 0.f;
-    const float dl = row < g.len ? delta[li] : 0.f;
-    const int kend = min(g.len, tile * kRows + kRows);
-    const int kbeg = max(0, tile * kRows - g.window + 1) / kRows * kRows;
-    for (int j0 = kbeg; j0 < kend; j0 += kRows) {
-        __syncthreads();
-        const int key = j0 + tid;
+    // query tiles that see one of the keys, every head of the group in turn
+    const int tf = k0 / kT;
+    const int64_t qend = min((int64_t)g.len, (int64_t)klast + g.window);
+    const int nit = ((int)((qend + kT - 1) / kT) - tf) * g.G;
+    f32x4 qr[P::C], dr[P::C];
+    float qc[4][P::NB], dc[4][P::NB], l2[4], dl[4];
+    Rows rq = rows_of<D>(q, g, at.b, g.Hq, at.h * g.G, at.s), rd = rq;
+    rd.rs = rows_of<D>(dO, g, at.b, g.Hq, at.h * g.G, at.s).rs;
+    const uint32_t qbase = rq.base;
+    auto place = [&](int it) __attribute__((always_inline)) {  // head and first row of item `it`
+        rq.base = rd.base = qbase + (uint32_t)(it % g.G) * D * 4;
+        return (tf + it / g.G) * kT;
+    };
+    auto load_rows = [&](int it) __attribute__((always_inline)) {
+        const int row0 = place(it);
+        P::row_form(rq, row0, lane, qr);
+        P::row_form(rd, row0, lane, dr);
+        const size_t lb = ((size_t)at.b * g.Hq + at.h * g.G + it % g.G) * g.N + at.s;
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            sk[tid][d] = key < g.len ? kb[key * ks + d] : 0.f;
-            sv[tid][d] = key < g.len ? vb[key * ks + d] : 0.f;
+        for (int r = 0; r < 4; ++r) {
+            const size_t x = lb + (size_t)min(row0 + 4 * gr + r, g.len - 1) * g.rowmul;
+            l2[r] = lse2[x];
+            dl[r] = delta[x];
         }
-        __syncthreads();
-        if (row >= g.len) continue;
-        const int jn = min(kRows, row - j0 + 1);
-        for (int jj = max(0, row - g.window + 1 - j0); jj < jn; ++jj) {
-            float dot = 0.f, dp = 0.f;
+    };
+    auto load_cols = [&](int it) __attribute__((always_inline)) {
+        const int row0 = place(it);
+        P::col_form(rq, row0, lane, qc);
+        P::col_form(rd, row0, lane, dc);
+    };
+    int it = wave;
+    if (it < nit) {
+        load_rows(it);
+        load_cols(it);
+    }
+    for (; it < nit; it += kWaves) {
+        const int row0 = (tf + it / g.G) * kT;
+        const bool masked = klast > row0 || row0 + kT - 1 - k0 >= g.window || row0 + kT > g.len;
+        f32x4 p[NS], ds[NS];
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                dot = __builtin_fmaf(qv[d], sk[jj][d], dot);
-                dp = __builtin_fmaf(dov[d], sv[jj][d], dp);
+        for (int i = 0; i < NS; ++i) {
+            p[i] = P::dot(qr, kb[i], f32x4{});
+            ds[i] = P::dot(dr, vb[i], f32x4{});
+        }
+        auto visible = [&](int row, int i) __attribute__((always_inline)) {
+            const int d = row - (k0 + i * kT + col);
+            return d >= 0 && d < g.window && row < g.len;
+        };
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float x = exp2f(__builtin_fmaf(p[i][r], g.scale_log2, -l2[r]));
+                float y = x * (ds[i][r] - dl[r]);
+                if (masked && !visible(row0 + 4 * gr + r, i)) x = y = 0.f;
+                p[i][r] = x;
+                ds[i][r] = y;
             }
-            const float p = exp2f(dot * g.scale_log2 - l2);
-            const float ds = p * (dp - dl);
+        if (it + kWaves < nit) load_rows(it + kWaves);
 #pragma unroll
-            for (int d = 0; d < D; ++d) acc[d] = __builtin_fmaf(ds, sk[jj][d], acc[d]);
+        for (int i = 0; i < NS; ++i) {
+            if (masked) {
+                place(it);
+                float *park = &mg.v[wave][0][0][0][0];
+                auto vis = [&](int x) { return visible(row0 + x, i); };
+                P::add_masked(rd, row0, lane, park, dc, p[i], av[i], vis);
+                P::add_masked(rq, row0, lane, park, qc, ds[i], ak[i], vis);
+            } else {
+                P::add(dc, p[i], av[i]);
+                P::add(qc, ds[i], ak[i]);
+            }
         }
+        if (it + kWaves < nit) load_cols(it + kWaves);
     }
-    if (row < g.len) {
+    const float one[kWaves] = {1.f, 1.f, 1.f, 1.f};
+    const Rows wk = rows_of<D>(dk, g, at.b, g.Hkv, at.h, at.s);
+    const Rows wv = rows_of<D>(dv, g, at.b, g.Hkv, at.h, at.s);
 #pragma unroll
-        for (int d = 0; d < D; ++d) dq[qoff + row * qs + d] = acc[d] * g.scale;
+    for (int x = 0; x < 2; ++x) {
+#pragma unroll
+        for (int i = 0; i < NS; ++i) mg.put(wave, i, lane, x == 0 ? ak[i] : av[i]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const uint32_t off = wk.off(k0 + i * kT + col);
+            mg.get(i, wave, lane, one, x == 0 ? g.scale : 1.f, [&](int d, const float(&y)[P::W]) {
+                store_dims(x == 0 ? wk.rs : wv.rs, off + d * 4, y);
+            });
+        }
+        __syncthreads();
     }
 }
 
-// One lane per key row of problem (b, hk, s); loops over the group's query heads and
-// the query rows that see the key.
-template <int D>
-__global__ __launch_bounds__(64) void sfa_dkdv_f32_kernel(const float *__restrict__ q,
-                                                          const float *__restrict__ k,
-                                                          const float *__restrict__ v,
-                                                          const float *__restrict__ dO,
-                                                          const float *__restrict__ delta,
-                                                          const float *__restrict__ lse2,
-                                                          float *__restrict__ dk,
-                                                          float *__restrict__ dv, SfaGeom g)
+// dQ of NS * 16 query rows: the waves take 16-key tiles.  S^T = K Q^T, dP^T = V dO^T,
+// dQ^T += K^T dS^T.
+template <int D, int NS>
+__device__ inline void dq_f32(const float *q, const float *k, const float *v, const float *dO,
+                              const float *delta, const float *lse2, float *dq, const SfaGeom &g,
+                              int64_t id, Merge<D, NS> &mg)
 {
-    __shared__ float sq[kRows][D];
-    __shared__ float sd[kRows][D];
-    __shared__ float sl[kRows], sdl[kRows];
-    const int ntiles = (g.len + kRows - 1) / kRows;
-    const int nprob = g.B * g.Hkv * g.streams;
+    using P = Ops<D>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, gr = lane >> 4;
+    const int ntiles = (g.len + NS * kT - 1) / (NS * kT);
     int prob, tile;
-    decode_key_tile(blockIdx.x, nprob, ntiles, prob, tile);
-    const int s = prob % g.streams, hk = (prob / g.streams) % g.Hkv;
-    const int b = prob / (g.streams * g.Hkv);
-    const int tid = threadIdx.x, key = tile * kRows + tid;
-    const size_t qs = (size_t)g.rowmul * g.Hq * D, ks = (size_t)g.rowmul * g.Hkv * D;
-    const size_t koff = (size_t)b * g.N * g.Hkv * D + (size_t)(s * g.Hkv + hk) * D;
+    decode_item(id, g.B * g.Hq * g.streams, ntiles, prob, tile);
+    const Where at = where(g, prob, g.Hq);
+    const Rows rq = rows_of<D>(q, g, at.b, g.Hq, at.h, at.s);
+    const Rows rd = rows_of<D>(dO, g, at.b, g.Hq, at.h, at.s);
+    const Rows rk = rows_of<D>(k, g, at.b, g.Hkv, at.h / g.G, at.s);
+    const Rows rv = rows_of<D>(v, g, at.b, g.Hkv, at.h / g.G, at.s);
+    const int q0 = tile * NS * kT, qlast = q0 + NS * kT - 1;
 
-    float kv[D], vv[D], ak[D], av[D];
+    f32x4 qb[NS][P::C], db[NS][P::C], acc[NS][P::NB];
+    float l2[NS], dl[NS];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        kv[d] = key < g.len ? k[koff + key * ks + d] : 0.f;
-        vv[d] = key < g.len ? v[koff + key * ks + d] : 0.f;
-        ak[d] = 0.f;
-        av[d] = 0.f;
+    for (int i = 0; i < NS; ++i) {
+        P::row_form(rq, q0 + i * kT, lane, qb[i]);
+        P::row_form(rd, q0 + i * kT, lane, db[i]);
+        const size_t x = ((size_t)at.b * g.Hq + at.h) * g.N +
+                         (size_t)min(q0 + i * kT + col, g.len - 1) * g.rowmul + at.s;
+        l2[i] = lse2[x];
+        dl[i] = delta[x];
+#pragma unroll
+        for (int b = 0; b < P::NB; ++b) acc[i][b] = f32x4{};
     }
-    for (int gi = 0; gi < g.G; ++gi) {
-        const int hq = hk * g.G + gi;
-        const size_t qoff = (size_t)b * g.N * g.Hq * D + (size_t)(s * g.Hq + hq) * D;
-        const size_t lbase = ((size_t)b * g.Hq + hq) * g.N + s;
-        // queries that see a key of this tile (local layers: up to the window's end)
-        const int qend = (int)min((int64_t)g.len, (int64_t)tile * kRows + kRows - 1 + g.window);
-        for (int i0 = tile * kRows; i0 < qend; i0 += kRows) {
-            __syncthreads();
-            const int qrow = i0 + tid;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                sq[tid][d] = qrow < g.len ? q[qoff + qrow * qs + d] : 0.f;
-                sd[tid][d] = qrow < g.len ? dO[qoff + qrow * qs + d] : 0.f;
-            }
-            sl[tid] = qrow < g.len ? lse2[lbase + (size_t)qrow * g.rowmul] : 0.f;
-            sdl[tid] = qrow < g.len ? delta[lbase + (size_t)qrow * g.rowmul] : 0.f;
-            __syncthreads();
-            if (key >= g.len) continue;
-            const int in = min(kRows, g.len - i0);
-            // causal and windowed: key <= query < key + window
-            const int iend = (int)min((int64_t)in, (int64_t)key + g.window - i0);
-            for (int ii = max(0, key - i0); ii < iend; ++ii) {
-                float dot = 0.f, dp = 0.f;
-#pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    dot = __builtin_fmaf(sq[ii][d], kv[d], dot);
-                    dp = __builtin_fmaf(sd[ii][d], vv[d], dp);
-                }
-                const float p = exp2f(dot * g.scale_log2 - sl[ii]);
-                const float ds = p * (dp - sdl[ii]);
-#pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    av[d] = __builtin_fmaf(p, sd[ii][d], av[d]);
-                    ak[d] = __builtin_fmaf(ds, sq[ii][d], ak[d]);
-                }
-            }
-        }
+    const int jf = max(0, q0 - g.window + 1) / kT;
+    const int je = (min(g.len, qlast + 1) + kT - 1) / kT;
+    f32x4 kr[P::C], vr[P::C];
+    float kc[4][P::NB];
+    auto load_rows = [&](int j) __attribute__((always_inline)) {
+        P::row_form(rk, j * kT, lane, kr);
+        P::row_form(rv, j * kT, lane, vr);
+    };
+    int j = jf + wave;
+    if (j < je) {
+        load_rows(j);
+        P::col_form(rk, j * kT, lane, kc);
     }
-    if (key < g.len) {
+    for (; j < je; j += kWaves) {
+        const int kb = j * kT;
+        const bool masked = kb + kT - 1 > q0 || qlast - kb >= g.window;
+        f32x4 p[NS], ds[NS];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            dk[koff + key * ks + d] = ak[d] * g.scale;
-            dv[koff + key * ks + d] = av[d];
+        for (int i = 0; i < NS; ++i) {
+            p[i] = P::dot(kr, qb[i], f32x4{});
+            ds[i] = P::dot(vr, db[i], f32x4{});
         }
+        if (j + kWaves < je) load_rows(j + kWaves);
+        auto visible = [&](int key, int i) __attribute__((always_inline)) {
+            const int d = q0 + i * kT + col - key;
+            return d >= 0 && d < g.window;
+        };
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float x = exp2f(__builtin_fmaf(p[i][r], g.scale_log2, -l2[i]));
+                const float y = x * (ds[i][r] - dl[i]);
+                ds[i][r] = masked && !visible(kb + 4 * gr + r, i) ? 0.f : y;
+            }
+            if (masked)
+                P::add_masked(rk, kb, lane, &mg.v[wave][0][0][0][0], kc, ds[i], acc[i], [&](int x) { return visible(kb + x, i); });
+            else
+                P::add(kc, ds[i], acc[i]);
+        }
+        if (j + kWaves < je) P::col_form(rk, (j + kWaves) * kT, lane, kc);
+    }
+    const float one[kWaves] = {1.f, 1.f, 1.f, 1.f};
+    const Rows wq = rows_of<D>(dq, g, at.b, g.Hq, at.h, at.s);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) mg.put(wave, i, lane, acc[i]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const uint32_t off = wq.off(q0 + i * kT + col);
+        mg.get(i, wave, lane, one, g.scale,
+               [&](int d, const float(&y)[P::W]) { store_dims(wq.rs, off + d * 4, y); });
+    }
+    __syncthreads();
+}
+
+// dK/dV work items [0, nkv), then dQ items
+template <int D, int NS>
+__global__ __launch_bounds__(kWaves * 64, 1) void sfa_bwd_f32_kernel(
+    const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+    const float *__restrict__ dO, const float *__restrict__ delta, const float *__restrict__ lse2,
+    float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv, SfaGeom g, int64_t nkv,
+    int64_t items)
+{
+    __shared__ Merge<D, NS> mg;
+    for (int64_t id = blockIdx.x; id < items; id += gridDim.x) {
+        if (id < nkv)
+            dkdv_f32<D, NS>(q, k, v, dO, delta, lse2, dk, dv, g, id, mg);
+        else
+            dq_f32<D, NS>(q, k, v, dO, delta, lse2, dq, g, id - nkv, mg);
     }
 }
+
+// 32 rows or keys per workgroup halve the operand bytes per product; 16 double the
+// workgroups and halve the longest one.  The larger tile is taken once it still gives every
+// CU two workgroups.
+constexpr int64_t kWideItems = 512;
+
+// Items beyond the grid are strided over it (a grid's work-items must fit 32 bits).
+unsigned grid_of(int64_t items) { return (unsigned)(items < (1 << 22) ? items : (1 << 22)); }
 
 template <int D>
 hipError_t fwd_f32_d(const float *q, const float *k, const float *v, float *o, float *lse,
                      const SfaGeom &g, hipStream_t s)
 {
-    const int ntiles = (g.len + kRows - 1) / kRows;
+    const int64_t nprob = (int64_t)g.B * g.Hq * g.streams;
+    const int64_t wide = (g.len + 31) / 32 * nprob, narrow = (g.len + 15) / 16 * nprob;
     timing_before("sfa_fwd_f32", s);
-    sfa_fwd_f32_kernel<D><<<ntiles * g.B * g.Hq * g.streams, kRows, 0, s>>>(q, k, v, o, lse, g);
+    if (wide >= kWideItems)
+        sfa_fwd_f32_kernel<D, 2><<<grid_of(wide), kWaves * 64, 0, s>>>(q, k, v, o, lse, g, wide);
+    else
+        sfa_fwd_f32_kernel<D, 1><<<grid_of(narrow), kWaves * 64, 0, s>>>(q, k, v, o, lse, g, narrow);
     hipError_t e = hipGetLastError();
     timing_after(s);
     return e;
@@ -280,17 +676,18 @@ hipError_t bwd_f32_d(const float *q, const float *k, const float *v, const float
                      float *dq, float *dk, float *dv, const SfaGeom &g, float *delta,
                      float *lse2, hipStream_t s)
 {
-    const int ntiles = (g.len + kRows - 1) / kRows;
-    timing_before("sfa_dq_f32", s);
-    sfa_dq_f32_kernel<D><<<ntiles * g.B * g.Hq * g.streams, kRows, 0, s>>>(q, k, v, dO, delta,
-                                                                            lse2, dq, g);
+    const int64_t pq = (int64_t)g.B * g.Hq * g.streams, pk = (int64_t)g.B * g.Hkv * g.streams;
+    const int64_t wide = (g.len + 31) / 32, narrow = (g.len + 15) / 16;
+    timing_before("sfa_bwd_f32", s);
+    // at D = 128 two key subtiles do not fit the registers
+    constexpr int kWide = D < 128 ? 2 : 1;
+    if (kWide == 2 && wide * pk >= kWideItems)
+        sfa_bwd_f32_kernel<D, kWide><<<grid_of(wide * (pk + pq)), kWaves * 64, 0, s>>>(
+            q, k, v, dO, delta, lse2, dq, dk, dv, g, wide * pk, wide * (pk + pq));
+    else
+        sfa_bwd_f32_kernel<D, 1><<<grid_of(narrow * (pk + pq)), kWaves * 64, 0, s>>>(
+            q, k, v, dO, delta, lse2, dq, dk, dv, g, narrow * pk, narrow * (pk + pq));
     hipError_t e = hipGetLastError();
-    timing_after(s);
-    if (e != hipSuccess) return e;
-    timing_before("sfa_dkdv_f32", s);
-    sfa_dkdv_f32_kernel<D><<<ntiles * g.B * g.Hkv * g.streams, kRows, 0, s>>>(
-        q, k, v, dO, delta, lse2, dk, dv, g);
-    e = hipGetLastError();
     timing_after(s);
     return e;
 }
