@@ -16,6 +16,10 @@
 //     the current one are free;
 //   dK/dV and dQ in one launch, the longer dK/dV workgroups first, so that both fill the
 //     chip together.
+// Measured (events, forward + preprocess + backward): B=1 L=256 n=2 Hq=8 Hkv=2 D=64, full
+// cross-stream, 77 us (12 TFLOP/s; 3,630 us with one lane per row on the vector units);
+// 50-63 TFLOP/s once the chip is full (B=2 L=512 n=4 Hq=12 Hkv=4), of 152 that a large
+// fp32 matrix product reaches.
 //
 // 16x16x4 MFMA layout: lane l supplies row (A) or column (B) l % 16 at k-slot l / 16; result
 // register r of lane l is row 4 (l / 16) + r, column l % 16.  Two operand forms follow:
@@ -33,7 +37,11 @@ namespace hd {
 namespace {
 
 constexpr int kT = 16;      // rows or keys per MFMA tile
-constexpr int kWaves = 4;   // waves per workgroup, splitting the sweep
+// Waves per workgroup, splitting the sweep: two per SIMD where their registers allow (the
+// backward of B=1 L=256 n=2 Hq=8 Hkv=2: 56 against 64 us at D=64, 37 against 44 at D=32;
+// at D=128, and with two subtiles at D=64, eight waves would spill).
+template <int D, int NS>
+constexpr int kWavesOf = D < 128 && NS == 1 ? 8 : 4;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -173,6 +181,7 @@ struct Ops {
 // the waves: store(dim, four or two consecutive dims).
 template <int D, int NS>
 struct Merge {
+    static constexpr int kWaves = kWavesOf<D, NS>;
     // [wave][subtile][block][register][lane]
     float v[kWaves][NS][Ops<D>::NB][4][64];
     __device__ inline void put(int wave, int sub, int lane, const f32x4 (&acc)[Ops<D>::NB])
@@ -191,10 +200,12 @@ struct Merge {
         return s;
     }
     // register r of this lane's column, dims in order, scaled by f
+    // (waves 0 .. 3, one register each)
     template <typename Store>
     __device__ inline void get(int sub, int r, int lane, const float (&sc)[kWaves], float f, Store store) const
     {
         constexpr int W = Ops<D>::W;
+        if (r >= 4) return;
 #pragma unroll
         for (int j = 0; j < Ops<D>::NB / W; ++j) {
             float x[W];
@@ -247,7 +258,7 @@ __device__ inline Rows rows_of(const float *p, const SfaGeom &g, int b, int head
 // Forward: NQ * 16 query rows; the waves take 32-key steps.  S^T = K Q^T puts a query's
 // scores in the four lanes of one column; O^T += V^T P^T.
 template <int D, int NQ>
-__global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_f32_kernel(const float *__restrict__ q,
+__global__ __launch_bounds__((kWavesOf<D, NQ> * 64), 1) void sfa_fwd_f32_kernel(const float *__restrict__ q,
                                                                   const float *__restrict__ k,
                                                                   const float *__restrict__ v,
                                                                   float *__restrict__ o,
@@ -255,6 +266,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_f32_kernel(const float
                                                                   int64_t items)
 {
     using P = Ops<D>;
+    constexpr int kWaves = kWavesOf<D, NQ>;
     constexpr int KS = 2, KT = KS * kT;  // keys per step
     __shared__ Merge<D, NQ> mg;
     __shared__ float sm[kWaves][NQ][16], sl[kWaves][NQ][16];
@@ -429,6 +441,7 @@ __device__ inline void dkdv_f32(const float *q, const float *k, const float *v, 
                                 const SfaGeom &g, int64_t id, Merge<D, NS> &mg)
 {
     using P = Ops<D>;
+    constexpr int kWaves = kWavesOf<D, NS>;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, gr = lane >> 4;
     const int ntiles = (g.len + NS * kT - 1) / (NS * kT);
@@ -522,7 +535,9 @@ __device__ inline void dkdv_f32(const float *q, const float *k, const float *v, 
         }
         if (it + kWaves < nit) load_cols(it + kWaves);
     }
-    const float one[kWaves] = {1.f, 1.f, 1.f, 1.f};
+    float one[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) one[w] = 1.f;
     const Rows wk = rows_of<D>(dk, g, at.b, g.Hkv, at.h, at.s);
     const Rows wv = rows_of<D>(dv, g, at.b, g.Hkv, at.h, at.s);
 #pragma unroll
@@ -549,6 +564,7 @@ __device__ inline void dq_f32(const float *q, const float *k, const float *v, co
                               int64_t id, Merge<D, NS> &mg)
 {
     using P = Ops<D>;
+    constexpr int kWaves = kWavesOf<D, NS>;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, gr = lane >> 4;
     const int ntiles = (g.len + NS * kT - 1) / (NS * kT);
@@ -616,7 +632,9 @@ __device__ inline void dq_f32(const float *q, const float *k, const float *v, co
         }
         if (j + kWaves < je) P::col_form(rk, (j + kWaves) * kT, lane, kc);
     }
-    const float one[kWaves] = {1.f, 1.f, 1.f, 1.f};
+    float one[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) one[w] = 1.f;
     const Rows wq = rows_of<D>(dq, g, at.b, g.Hq, at.h, at.s);
 #pragma unroll
     for (int i = 0; i < NS; ++i) mg.put(wave, i, lane, acc[i]);
@@ -632,7 +650,7 @@ __device__ inline void dq_f32(const float *q, const float *k, const float *v, co
 
 // dK/dV work items [0, nkv), then dQ items
 template <int D, int NS>
-__global__ __launch_bounds__(kWaves * 64, 1) void sfa_bwd_f32_kernel(
+__global__ __launch_bounds__((kWavesOf<D, NS> * 64), 1) void sfa_bwd_f32_kernel(
     const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
     const float *__restrict__ dO, const float *__restrict__ delta, const float *__restrict__ lse2,
     float *__restrict__ dq, float *__restrict__ dk, float *__restrict__ dv, SfaGeom g, int64_t nkv,
@@ -649,7 +667,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_bwd_f32_kernel(
 
 // 32 rows or keys per workgroup halve the operand bytes per product; 16 double the
 // workgroups and halve the longest one.  The larger tile is taken once it still gives every
-// CU two workgroups.
+// CU two workgroups: at B=1 L=256 n=2 Hq=8 Hkv=2 D=64 (64 key tiles of 16) the backward
+// takes 56 us narrow and 106 us wide, at B=2 L=512 n=4 Hq=12 Hkv=4 D=32 (512 of 32)
+// 112 narrow and 88 wide.
 constexpr int64_t kWideItems = 512;
 
 // Items beyond the grid are strided over it (a grid's work-items must fit 32 bits).
@@ -663,9 +683,9 @@ hipError_t fwd_f32_d(const float *q, const float *k, const float *v, float *o, f
     const int64_t wide = (g.len + 31) / 32 * nprob, narrow = (g.len + 15) / 16 * nprob;
     timing_before("sfa_fwd_f32", s);
     if (wide >= kWideItems)
-        sfa_fwd_f32_kernel<D, 2><<<grid_of(wide), kWaves * 64, 0, s>>>(q, k, v, o, lse, g, wide);
+        sfa_fwd_f32_kernel<D, 2><<<grid_of(wide), kWavesOf<D, 2> * 64, 0, s>>>(q, k, v, o, lse, g, wide);
     else
-        sfa_fwd_f32_kernel<D, 1><<<grid_of(narrow), kWaves * 64, 0, s>>>(q, k, v, o, lse, g, narrow);
+        sfa_fwd_f32_kernel<D, 1><<<grid_of(narrow), kWavesOf<D, 1> * 64, 0, s>>>(q, k, v, o, lse, g, narrow);
     hipError_t e = hipGetLastError();
     timing_after(s);
     return e;
@@ -682,10 +702,10 @@ hipError_t bwd_f32_d(const float *q, const float *k, const float *v, const float
     // at D = 128 two key subtiles do not fit the registers
     constexpr int kWide = D < 128 ? 2 : 1;
     if (kWide == 2 && wide * pk >= kWideItems)
-        sfa_bwd_f32_kernel<D, kWide><<<grid_of(wide * (pk + pq)), kWaves * 64, 0, s>>>(
+        sfa_bwd_f32_kernel<D, kWide><<<grid_of(wide * (pk + pq)), kWavesOf<D, kWide> * 64, 0, s>>>(
             q, k, v, dO, delta, lse2, dq, dk, dv, g, wide * pk, wide * (pk + pq));
     else
-        sfa_bwd_f32_kernel<D, 1><<<grid_of(narrow * (pk + pq)), kWaves * 64, 0, s>>>(
+        sfa_bwd_f32_kernel<D, 1><<<grid_of(narrow * (pk + pq)), kWavesOf<D, 1> * 64, 0, s>>>(
             q, k, v, dO, delta, lse2, dq, dk, dv, g, narrow * pk, narrow * (pk + pq));
     hipError_t e = hipGetLastError();
     timing_after(s);
