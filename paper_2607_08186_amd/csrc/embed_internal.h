@@ -9,12 +9,13 @@ namespace hd {
 // Gradient of the expansion with respect to the tables (see embed_bwd.hip).  Workspace
 // byte offsets for M = B*L tokens, each part 256-byte aligned: two (key, token) buffer
 // pairs of the radix sort, digit histograms, scan block sums, a few scalars, segment
-// indices and segment starts (M + 1 entries).
+// indices, and M + 1 more entries that are not used (callers keep workspaces of this size).
 struct EmbedBwdWorkspace {
-    size_t keys_a, vals_a, keys_b, vals_b, hist, sums, scalars, segidx, seg_start, total;
+    size_t keys_a, vals_a, keys_b, vals_b, hist, sums, scalars, segidx, total;
 };
 constexpr int kEmbedBwdMaxTokens = 2048 * 2048;  // B*L limit of the single-level scans
-constexpr int kSmallSortMax = 16384;              // B*L up to which one counting pass sorts
+constexpr int kSmallSortMax = 8192;               // B*L up to which one counting pass sorts
+constexpr int kMidSortMax = 131072;               // B*L up to which few-launch radix passes sort
 EmbedBwdWorkspace embed_bwd_workspace(int M);
 hipError_t launch_embed_bwd(const int32_t *ids, const void *dout, int B, int L, int n, int64_t V,
                             int Dm, int esize, int32_t *uniq, float *drows, int32_t *num_uniq,
