@@ -65,6 +65,19 @@ __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Lets every MFMA issued so far finish (24 wait states; a 32x32x16 bf16 result is readable
+// after 11, a 16x16x4 fp32 one after 10).  The compiler places these wait states itself, but
+// where a branch separates an MFMA from the first read of its result it has counted them
+// along the longer path into the join only, and the shorter one then read the last result
+// registers too early.  So kernels put this (or `pin` the result, in the MFMA's own block)
+// before such a branch or right after it.
+__device__ inline void mfma_settle()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Two floats -> packed bf16x2 (round to nearest even), low half = a.
 __device__ inline uint32_t pack_bf16(float a, float b)
 {

@@ -10,13 +10,19 @@
 // HBM-bound: every cached key/value row is read once for all the query rows that use it
 // (the heads of its group, and for cross-stream layers all n streams: up to 32 query
 // slots per problem).  Split over the cache:
-//   partial: a workgroup takes 256 cached rows of one problem (b, kv-head[, head chunk]
-//            [, stream]), one 64-row tile per wave, K to registers and V to LDS (all
-//            loads issued up front; two workgroups per CU, so one's loads overlap the
-//            other's arithmetic), S^T = K Q^T and O^T += V^T P^T on the matrix cores,
-//            the four waves merged through LDS into one (max, sum, unnormalised O) per
-//            query slot in the workspace;
-//   combine: per query row, the chunks' partials reduced to o and lse.
+//   partial: a workgroup takes one split of the cached rows of one problem (b, kv-head[,
+//            head chunk][, stream]); its waves take 32-row tiles in turn, each through a ring of
+//            its own in LDS that holds two tiles of K and V (direct-to-LDS streaming loads
+//            of whole lines, the next tile in flight while one is used, no barrier in the
+//            loop), S^T = K Q^T and O^T += V^T P^T on the matrix cores with a running
+//            maximum per query slot, the waves merged through LDS into one (max, sum,
+//            unnormalised O) per query slot in the workspace;
+//   combine: per query row, the splits' partials reduced to o and lse.
+// Where a problem has one split only (short contexts, or enough problems to fill the chip) the
+// partial kernel writes o and lse itself and the combine is not launched.
+// Measured at 16 x 4096 tokens, n=4, 32/8 heads of 128: 6.1 TB/s of cache rows with the combine
+// (full cross-stream and intra-stream), against 4.4 and 5.2 TB/s with one 256-row workgroup per
+// partial and K loaded straight to registers; streaming loads give 5% over cached ones.
 #include <mutex>
 
 #include "decode_internal.h"
@@ -26,8 +32,7 @@ namespace hd {
 
 namespace {
 
-constexpr int kDecWaves = 4;
-constexpr int kDecChunk = kDecWaves * kRows;  // cached rows per workgroup
+constexpr int kTile = 32;                     // cached rows per wave and step
 constexpr int kSlots = 32;                    // query slots per problem (MFMA columns)
 
 // problem index -> (b, kv head, head chunk, stream) and the problem's query slots:
@@ -52,31 +57,60 @@ __device__ inline DecProblem dec_problem(const DecGeom &g, int p)
     return r;
 }
 
-template <int D>
-__global__ __launch_bounds__(kDecWaves * 64, 2) void sfa_decode_partial_kernel(
+// cached rows of a problem that some query row of it sees: [klo, kvlen), the first one
+// rounded down to a tile; they are split over nsplit workgroups, `per` rows each
+struct DecRows {
+    int klo, kvlen, per;
+};
+
+__device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
+{
+    DecRows r;
+    r.kvlen = g.mode == 0 ? ctx + 1 : (ctx + 1) * g.n;
+    r.klo = (g.mode == 2 ? max(0, ctx * g.n - g.window + 1) : 0) / kTile * kTile;
+    r.per = dec_split_rows(g.problems, g.D, r.kvlen - r.klo);
+    return r;
+}
+
+template <int N>
+__device__ inline void wait_loads_le()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ kc, const bf16 *__restrict__ vc,
-    const int32_t *__restrict__ ctx_tokens, float *__restrict__ part, DecGeom g)
+    const int32_t *__restrict__ ctx_tokens, float *__restrict__ part, bf16 *__restrict__ o,
+    float *__restrict__ lse, DecGeom g)
 {
     constexpr int KS = D / 16, DB = D / 32;
-    using T = Tile<D>;
-    // LDS: the V tile of each wave (read transposed), reused at the end as the scratch of
-    // the merge of the four waves ([wave][slot][D] of O, then [wave][slot] max and sum)
-    constexpr int MERGE = kDecWaves * kSlots * D * 4 + 2 * kDecWaves * kSlots * 4;
-    static_assert(MERGE >= kDecWaves * T::BYTES, "V tiles must fit in the merge scratch");
-    __shared__ __attribute__((aligned(1024))) char smem[MERGE];
+    using T = Tile<D, kTile>;
+    constexpr int STAGE = 2 * T::BYTES;  // K rows | V rows
+    constexpr int LOADS = 2 * T::INSTR;  // direct-to-LDS instructions per stage
+    // the rings, reused at the end as the scratch of the merge ([wave][slot][D + 1] of O:
+    // the odd row length keeps both its writes, a slot per lane, and its reads, a dim per
+    // lane, off one another's banks; then [wave][slot] max and sum)
+    constexpr int MERGE = NW * kSlots * (D + 1) * 4 + 2 * NW * kSlots * 4;
+    constexpr int RING = NW * 2 * STAGE;
+    __shared__ __attribute__((aligned(1024))) char smem[MERGE > RING ? MERGE : RING];
 
-    const int chunk = blockIdx.x;
     const DecProblem pr = dec_problem(g, blockIdx.y);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
 
     const int ctx = ctx_tokens[pr.b];
-    // cached rows of the problem: cross-stream rows 0 .. (ctx+1)n - 1; intra-stream rows
-    // j*n + s for j <= ctx (problem row j)
-    const int kvlen = g.mode == 0 ? ctx + 1 : (ctx + 1) * g.n;
+    const DecRows dr = dec_rows(g, ctx);
     const int pos0 = ctx * g.n;  // expanded position of the new token's stream 0
-    const int kb = chunk * kDecChunk + wave * kRows;  // first problem row of my tile
+    // this workgroup's rows: cross-stream rows are expanded positions, intra-stream problem
+    // row j is cache row j*n + s
+    const int r0 = dr.klo + (int)blockIdx.x * dr.per;
+    if (r0 >= dr.kvlen) return;  // the combine reads the splits that have rows
+    const int r1 = min(dr.kvlen, r0 + dr.per);
+    const int nt = (r1 - r0 + kTile - 1) / kTile;
 
     const size_t cslice = (size_t)g.n * g.Lcap * g.Hkv * D;  // one sequence's cache
     const rsrc_t rk = make_rsrc(kc + pr.b * cslice, (uint32_t)(cslice * 2));
@@ -84,148 +118,181 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void sfa_decode_partial_kernel(
     const uint32_t kstride = (uint32_t)(g.mode == 0 ? g.n : 1) * g.Hkv * D * 2;
     const uint32_t kbase = (uint32_t)((g.mode == 0 ? pr.s : 0) * g.Hkv + pr.hk) * D * 2;
 
-    // first row any query row sees: 0, or for local layers the window start of stream 0
-    const int klo = g.mode == 2 ? max(0, pos0 - g.window + 1) : 0;
-    // a chunk without a visible row is skipped whole; the combine reads only the chunks
-    // from klo / kDecChunk to the last row
-    const int c0 = chunk * kDecChunk;
-    if (c0 >= kvlen || c0 + kDecChunk - 1 < klo) return;
-    // wave-uniform: my tile holds a visible row (else it is neither loaded nor used)
-    const bool any = kb < kvlen && kb + kRows - 1 >= klo;
-    // K rows go straight to registers as the A operand of S^T = K Q^T (lane: row l32 of
-    // block mb, dims kk*16 + hi*8 ..); V moves to LDS by direct loads for the transposed
-    // reads of the P V product.  Rows past kvlen read zeros.
-    char *vtile = smem + wave * T::BYTES;
-    bf16x8 ka[2][KS];
-    if (any) {
-        T::load(vtile, rv, kbase, kstride, kb, kvlen, 0, 1, lane);
+    char *const ring = smem + wave * 2 * STAGE;
+    const auto plan = T::template dma_plan<1>(kbase, kstride, 0, lane);
+    // tile t of the split into stage t / NW % 2; rows past the context load zeros.  Whole
+    // lines read once: streaming loads, unless another head chunk reads the rows too.
+    auto issue = [&](int t, char *st) __attribute__((always_inline)) {
+        const int row0 = r0 + t * kTile;
+        const uint32_t off = (uint32_t)row0 * kstride;
+        const bool whole = row0 + kTile <= dr.kvlen, once = g.ngc == 1;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            const int row = kb + mb * 32 + l32;
-            const uint32_t off = row < kvlen ? kbase + (uint32_t)row * kstride : kOob;
+        for (int i = 0; i < T::INSTR; ++i) {
+            uint32_t x = plan.voff[i] + off;
+            if (!whole && row0 + (i * 64 + lane) / T::CH >= dr.kvlen) x = kOob;
+            if (once) {
+                dma_lds16_nt(rk, st + i * 1024, x);
+                dma_lds16_nt(rv, st + T::BYTES + i * 1024, x);
+            } else {
+                dma_lds16(rk, st + i * 1024, x);
+                dma_lds16(rv, st + T::BYTES + i * 1024, x);
+            }
+        }
+    };
+
+    // The 32 query slots (column l32 of the MFMA results is slot l32) come through the ring's
+    // second stage, behind them the first tile.
+    const int nslot = g.nslot;
+    {
+        const rsrc_t rq = make_rsrc(q, (uint32_t)((size_t)g.B * g.n * g.Hq * D * 2));
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                ka[mb][kk] = __builtin_bit_cast(bf16x8, ld16(rk, off + (kk * 16 + hi * 8) * 2));
+        for (int i = 0; i < T::INSTR; ++i) {
+            const int x = i * 64 + lane, slot = x / T::CH, c = (x % T::CH) ^ T::swz(slot);
+            const int st = g.mode == 0 ? pr.s : slot / g.gchunk;
+            const int h = pr.hk * g.G + pr.gc * g.gchunk + (g.mode == 0 ? slot : slot % g.gchunk);
+            dma_lds16(rq, ring + STAGE + i * 1024,
+                      slot < nslot ? (uint32_t)((((size_t)pr.b * g.n + st) * g.Hq + h) * D * 2) + c * 16 : kOob);
         }
     }
-
-    // my query slot (column l32 of the MFMA results): its head and stream
-    const int nslot = g.nslot;
-    const int slot = l32;
-    const int sl_s = g.mode == 0 ? pr.s : slot / g.gchunk;
-    const int hq = pr.hk * g.G + pr.gc * g.gchunk + (g.mode == 0 ? slot : slot % g.gchunk);
-    const int qp = pos0 + sl_s;  // key coordinate of my query (cross-stream layers)
-    bf16x8 qr[KS];
-    {
-        const size_t qslice = (size_t)g.B * g.n * g.Hq * D;
-        const rsrc_t rq = make_rsrc(q, (uint32_t)(qslice * 2));
-        const uint32_t off =
-            slot < nslot ? (uint32_t)((((size_t)pr.b * g.n + sl_s) * g.Hq + hq) * D * 2) : kOob;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk)
-            qr[kk] = __builtin_bit_cast(bf16x8, ld16(rq, off + (kk * 16 + hi * 8) * 2));
+    int t = wave;
+    if (t < nt) {
+        issue(t, ring);
+        wait_loads_le<LOADS>();
+    } else {
+        wait_loads_le<0>();
     }
-    wait_lds_loads();
-    __syncthreads();
+    uint32_t kro[KS], vto[DB][2];
+    T::row_offsets(l32, hi, kro);
+    T::tr_offsets(lane, vto);
+    bf16x8 qr[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) qr[kk] = T::row_at(ring + STAGE, kro[kk], 0);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) pin(qr[kk]);
+    __builtin_amdgcn_sched_barrier(0);
 
-    // S^T = K Q^T for my 64 rows (two blocks of 32), then the mask: a row is visible if
-    // it exists and, for cross-stream layers, lies at or before my query and within
-    // the window.  A tile without a visible row contributes an empty partial.
-    float mx = -INFINITY, lsum = 0.f;
+    float m = -INFINITY, lsum = 0.f;
     f32x16 oacc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
-    if (any) {
-        f32x16 sc[2];
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            sc[mb] = f32x16{};
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                sc[mb] = mfma32(ka[mb][kk], qr[kk], sc[mb]);
+    const float c2 = g.scale_log2;
+    const int qp = pos0 + (g.mode == 0 ? 0 : l32 / g.gchunk);  // my query's key coordinate
+    for (int i = 0; t < nt; ++i, t += NW) {
+        char *const st = ring + (i & 1) * STAGE;
+        if (t + NW < nt) {
+            issue(t + NW, ring + ((i + 1) & 1) * STAGE);
+            wait_loads_le<LOADS>();
+        } else {
+            wait_loads_le<0>();
         }
-        const float c2 = g.scale_log2;
+        const int kb = r0 + t * kTile;
+        // S^T = K Q^T, then the mask: a row is visible if it exists and, for cross-stream
+        // layers, lies at or before my query and within the window
+        f32x16 sc = {};
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int kk = 0; kk < KS; ++kk) sc = mfma32(T::row_at(st, kro[kk], 0), qr[kk], sc);
+        mfma_settle();
+        const int last = kb + kTile - 1;
+        const bool masked = last >= dr.kvlen ||
+                            (g.mode != 0 && (last > pos0 || pos0 + g.n - 1 - kb >= g.window));
+        float mx = -INFINITY;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = kb + mb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-                bool vis = j < kvlen && slot < nslot;
+        for (int r = 0; r < 16; ++r) {
+            float x = sc[r] * c2;
+            if (masked) {
+                const int j = kb + 8 * (r >> 2) + 4 * hi + (r & 3);
+                bool vis = j < dr.kvlen;
                 if (g.mode != 0) vis = vis && j <= qp && qp - j < g.window;
-                sc[mb][r] = vis ? sc[mb][r] * c2 : -INFINITY;
-                mx = fmaxf(mx, sc[mb][r]);
+                x = vis ? x : -INFINITY;
             }
-        mx = max_xor32(mx);
-        const float me = mx == -INFINITY ? 0.f : mx;  // no visible row: weights exp2(-inf) = 0
-        bf16x8 pb[4];
+            sc[r] = x;
+            mx = fmaxf(mx, x);
+        }
+        const float mn = fmaxf(m, max_xor32(mx));
+        if (__any(mn > m)) {
+            const float alpha = mn == m ? 1.f : fast_exp2(m - mn);
+            m = mn;
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) oacc[db] *= alpha;
+        }
+        const float me = m == -INFINITY ? 0.f : m;  // no visible row yet: weights exp2(-inf) = 0
+        bf16x8 pb[2];
         const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int h = 0; h < 2; ++h) {
+            uint32_t w[4];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t w[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    w[e] = pack_bf16(fast_exp2(sc[mb][h * 8 + 2 * e] - me),
-                                     fast_exp2(sc[mb][h * 8 + 2 * e + 1] - me));
-                    // the sum adds the bf16 weights that the P V product uses
-                    lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones,
-                                                           lsum, false);
-                }
-                pb[mb * 2 + h] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+            for (int e = 0; e < 4; ++e) {
+                w[e] = pack_bf16(fast_exp2(sc[h * 8 + 2 * e] - me), fast_exp2(sc[h * 8 + 2 * e + 1] - me));
+                // the sum adds the bf16 weights that the P V product uses
+                lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones, lsum, false);
             }
-        lsum = sum_xor32(lsum);
-        // O^T (dims x slots) = V^T P^T over my 64 rows
+            pb[h] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
+        }
+        // O^T (dims x slots) += V^T P^T
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-                oacc[db] = mfma32(T::tr_operand(vtile, db * 32, kk, lane), pb[kk], oacc[db]);
+            for (int kk = 0; kk < 2; ++kk)
+                oacc[db] = mfma32(T::tr_at(st + T::BYTES, vto[db], kk), pb[kk], oacc[db]);
+        // this stage is loaded again in the next step: its reads have completed
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
+    mfma_settle();
+    lsum = sum_xor32(lsum);
 
-    // merge the four waves: scratch [wave][slot][D] of O, then [wave][slot] max and sum
+    // merge the waves
     __syncthreads();
     float *so = reinterpret_cast<float *>(smem);
-    float *sm = so + kDecWaves * kSlots * D;
-    float *sl = sm + kDecWaves * kSlots;
+    float *sm = so + NW * kSlots * (D + 1);
+    float *sl = sm + NW * kSlots;
+    if (l32 < nslot) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int d = db * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-            so[(wave * kSlots + slot) * D + d] = oacc[db][r];
+            for (int r = 0; r < 16; ++r)
+                so[(wave * kSlots + l32) * (D + 1) + db * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)] = oacc[db][r];
+        if (hi == 0) {
+            sm[wave * kSlots + l32] = m;
+            sl[wave * kSlots + l32] = lsum;
         }
-    if (hi == 0) {
-        sm[wave * kSlots + slot] = mx;
-        sl[wave * kSlots + slot] = lsum;
     }
     __syncthreads();
-    // partials [problem][chunk][slot][D + 2]: O, then max and sum, for the problem's
-    // nslot slots only
-    float *dst = part + ((size_t)blockIdx.y * g.nchunk + chunk) * nslot * (D + 2);
-    for (int e = tid; e < nslot * D; e += kDecWaves * 64) {  // the problem's slots only
+    // partials [problem][split][slot][D + 2]: O, then max and sum, for the problem's
+    // nslot slots only; with one split per problem the results themselves
+    float *dst = part + ((size_t)blockIdx.y * g.nsplit + blockIdx.x) * nslot * (D + 2);
+    for (int e = tid; e < nslot * D; e += NW * 64) {
         const int sl_i = e / D, d = e % D;
-        float m = -INFINITY;
+        float mt = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kDecWaves; ++w) m = fmaxf(m, sm[w * kSlots + sl_i]);
-        float o = 0.f, l = 0.f;
-        if (m != -INFINITY) {
+        for (int w = 0; w < NW; ++w) mt = fmaxf(mt, sm[w * kSlots + sl_i]);
+        float x = 0.f, l = 0.f;
+        if (mt != -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < kDecWaves; ++w) {
-                const float a = fast_exp2(sm[w * kSlots + sl_i] - m);
-                o += a * so[(w * kSlots + sl_i) * D + d];
+            for (int w = 0; w < NW; ++w) {
+                const float a = fast_exp2(sm[w * kSlots + sl_i] - mt);
+                x += a * so[(w * kSlots + sl_i) * (D + 1) + d];
                 l += a * sl[w * kSlots + sl_i];
             }
         }
-        dst[sl_i * (D + 2) + d] = o;
-        if (d == 0) {
-            dst[sl_i * (D + 2) + D] = m;
-            dst[sl_i * (D + 2) + D + 1] = l;
+        if (g.nsplit == 1) {
+            const int st = g.mode == 0 ? pr.s : sl_i / g.gchunk;
+            const int h = pr.hk * g.G + pr.gc * g.gchunk + (g.mode == 0 ? sl_i : sl_i % g.gchunk);
+            o[(((size_t)pr.b * g.n + st) * g.Hq + h) * D + d] = (bf16)(x / l);
+            if (d == 0) lse[((size_t)pr.b * g.Hq + h) * g.n + st] = (mt + log2f(l)) * 0.6931471805599453f;
+        } else {
+            dst[sl_i * (D + 2) + d] = x;
+            if (d == 0) {
+                dst[sl_i * (D + 2) + D] = mt;
+                dst[sl_i * (D + 2) + D + 1] = l;
+            }
         }
     }
 }
 
-// one workgroup of D threads per query row (b, s, hq): reduce the chunks' partials
+// one workgroup of D threads per query row (b, s, hq): reduce the splits' partials
 template <int D>
 __global__ __launch_bounds__(D) void sfa_decode_combine_kernel(const float *__restrict__ part,
                                                                const int32_t *__restrict__ ctx_tokens,
@@ -244,29 +311,26 @@ __global__ __launch_bounds__(D) void sfa_decode_combine_kernel(const float *__re
     } else {
         slot = s * g.gchunk + gl;
     }
-    // the chunks the partial kernel wrote: those with a row in [klo, kvlen)
-    const int ctx = ctx_tokens[b];
-    const int kvlen = g.mode == 0 ? ctx + 1 : (ctx + 1) * g.n;
-    const int klo = g.mode == 2 ? max(0, ctx * g.n - g.window + 1) : 0;
-    const int nc = min(g.nchunk, (kvlen + kDecChunk - 1) / kDecChunk);
-    const int cl = klo / kDecChunk;
-    const float *src = part + (size_t)prob * g.nchunk * g.nslot * (D + 2) + slot * (D + 2);
+    // the splits the partial kernel wrote: those with rows
+    const DecRows dr = dec_rows(g, ctx_tokens[b]);
+    const int nc = (dr.kvlen - dr.klo + dr.per - 1) / dr.per;
+    const float *src = part + (size_t)prob * g.nsplit * g.nslot * (D + 2) + slot * (D + 2);
     const size_t cstep = (size_t)g.nslot * (D + 2);
-    // Every chunk in [cl, nc) has a visible row for some query of the problem, but
+    // Every split has a visible row for some query of the problem, but
     // possibly none for this one (max -inf, sum 0); the query's own key is in one of
     // them, so the largest maximum m is finite.  Two passes, m first and then each
-    // chunk's share scaled by exp2(mc - m): no load waits for the previous chunk's
+    // split's share scaled by exp2(mc - m): no load waits for the previous split's
     // arithmetic, as it would with a running maximum.
     float m = -INFINITY;
 #pragma unroll 8
-    for (int c = cl; c < nc; ++c) m = fmaxf(m, src[c * cstep + D]);
+    for (int c = 0; c < nc; ++c) m = fmaxf(m, src[c * cstep + D]);
     float acc = 0.f, l = 0.f;
 #pragma unroll 8
-    for (int c = cl; c < nc; ++c) {
+    for (int c = 0; c < nc; ++c) {
         const float mc = src[c * cstep + D], lc = src[c * cstep + D + 1];
         const float oc = src[c * cstep + threadIdx.x];
         const float w = fast_exp2(mc - m);  // exp2(-inf) = 0
-        // a chunk without a visible row is skipped (select, no branch)
+        // a split without a visible row is skipped (select, no branch)
         acc = mc == -INFINITY ? acc : __builtin_fmaf(oc, w, acc);
         l = mc == -INFINITY ? l : __builtin_fmaf(lc, w, l);
     }
@@ -298,6 +362,10 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     g.nchunk = (int)((rows + kDecChunk - 1) / kDecChunk);
     g.problems = B * Hkv * g.ngc * (mode == 0 ? n : 1);
     g.nslot = g.gchunk * per_head;
+    // the most splits any context up to max_ctx takes; a local layer's rows span at most
+    // the window, the other streams of the token and the rounding down to a tile
+    const int64_t span = mode == 2 && rows > (int64_t)g.window + n + kTile ? (int64_t)g.window + n + kTile : rows;
+    g.nsplit = dec_max_splits(g.problems, D, (int)span);
     return g;
 }
 
@@ -339,15 +407,18 @@ hipError_t launch_decode_bf16(const void *q, const void *kc, const void *vc, con
                *vv = static_cast<const bf16 *>(vc);
     float *part = static_cast<float *>(ws);
     bf16 *oo = static_cast<bf16 *>(o);
-    const dim3 grid(g.nchunk, g.problems);
+    const dim3 grid(g.nsplit, g.problems);
     const int rows = g.B * g.n * g.Hq;
     auto run = [&](auto dk, const char *pname, const char *cname) {
         constexpr int DD = decltype(dk)::value;
         timing_before(pname, s);
-        sfa_decode_partial_kernel<DD><<<grid, kDecWaves * 64, 0, s>>>(qq, kk, vv, ctx, part, g);
+        if (dec_wide(g.problems, DD, g.nsplit))
+            sfa_decode_partial_kernel<DD, 4><<<grid, 4 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+        else
+            sfa_decode_partial_kernel<DD, 2><<<grid, 2 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
         hipError_t e = hipGetLastError();
         timing_after(s);
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || g.nsplit == 1) return e;
         timing_before(cname, s);
         sfa_decode_combine_kernel<DD><<<rows, DD, 0, s>>>(part, ctx, oo, lse, g);
         e = hipGetLastError();

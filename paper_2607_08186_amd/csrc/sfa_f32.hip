@@ -143,6 +143,7 @@ struct Ops {
 #pragma unroll
             for (int b = 0; b < NB; ++b) bad = bad || not_finite(a[r][b]);
         if (__any(bad)) {
+            mfma_settle();
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -171,8 +172,10 @@ struct Ops {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
                     acc[b] = mfma16f(not_finite(a[r][b]) ? 0.f : a[r][b], w[r], acc[b]);
+            mfma_settle();
         } else {
             add(a, w, acc);
+            mfma_settle();
         }
     }
 };
@@ -318,6 +321,7 @@ __global__ __launch_bounds__((kWavesOf<D, NQ> * 64), 1) void sfa_fwd_f32_kernel(
             for (int t = 0; t < KS; ++t)
 #pragma unroll
                 for (int i = 0; i < NQ; ++i) sc[t][i] = P::dot(kr[t], qr[i], f32x4{});
+        mfma_settle();
             if (j + kWaves < je) load_k(j + kWaves);
             const bool masked = kb + KT - 1 > q0 || qlast - kb >= g.window;
             auto visible = [&](int key, int i) __attribute__((always_inline)) {
@@ -365,6 +369,7 @@ __global__ __launch_bounds__((kWavesOf<D, NQ> * 64), 1) void sfa_fwd_f32_kernel(
                         P::add(vc[t], sc[t][i], oacc[i]);
             if (j + kWaves < je) load_v(j + kWaves);
         }
+        mfma_settle();
         // merge the waves: the row's largest maximum, then each wave's share scaled to it
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
@@ -505,6 +510,7 @@ __device__ inline void dkdv_f32(const float *q, const float *k, const float *v, 
             p[i] = P::dot(qr, kb[i], f32x4{});
             ds[i] = P::dot(dr, vb[i], f32x4{});
         }
+        mfma_settle();
         auto visible = [&](int row, int i) __attribute__((always_inline)) {
             const int d = row - (k0 + i * kT + col);
             return d >= 0 && d < g.window && row < g.len;
@@ -535,6 +541,7 @@ __device__ inline void dkdv_f32(const float *q, const float *k, const float *v, 
         }
         if (it + kWaves < nit) load_cols(it + kWaves);
     }
+    mfma_settle();
     float one[kWaves];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) one[w] = 1.f;
@@ -612,6 +619,7 @@ __device__ inline void dq_f32(const float *q, const float *k, const float *v, co
             p[i] = P::dot(kr, qb[i], f32x4{});
             ds[i] = P::dot(vr, db[i], f32x4{});
         }
+        mfma_settle();
         if (j + kWaves < je) load_rows(j + kWaves);
         auto visible = [&](int key, int i) __attribute__((always_inline)) {
             const int d = q0 + i * kT + col - key;
@@ -632,6 +640,7 @@ __device__ inline void dq_f32(const float *q, const float *k, const float *v, co
         }
         if (j + kWaves < je) P::col_form(rk, (j + kWaves) * kT, lane, kc);
     }
+    mfma_settle();
     float one[kWaves];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) one[w] = 1.f;
