@@ -7,7 +7,7 @@
 // Tiling (gfx950, wave64):
 //   workgroup = 8 waves = 256 query rows of one problem (two waves per SIMD); wave w
 //   owns rows 32w..32w+31 and each lane keeps one query row (column l%32 of the MFMA
-//   results).  The transposed score tile S^T = K Q^T puts a row's scores in one lane,
+//   results).  (Small grids take 128-row blocks, see Shape.)  The transposed score tile S^T = K Q^T puts a row's scores in one lane,
 //   so the row max / row sum need one cross-half exchange, and P^T feeds the second
 //   MFMA (O^T += V^T P^T) straight from registers.
 //   Key/value tiles of 64 rows are loaded HBM -> LDS by direct-to-LDS buffer loads
@@ -34,20 +34,32 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // FINAL: final-stream layer (query row i at key coordinate i*n + n - 1, strided wave
 // rows); otherwise query row i is key coordinate i and waves take consecutive rows.
-template <int D, bool FINAL>
-__global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
+// Block shapes.  kPlain: 256 rows, one workgroup per CU at D >= 64.  kShared (D = 64): the same
+// held to 128 registers, so that two workgroups share a CU.  kSplit: a block holds 128 rows, both groups of waves own the same ones (wave w
+// and w + 4 rows 32w ..) and take every second key tile each, group B the odd ones, through
+// rings of their own; at the end group A adds group B's part, scaled to the common
+// reference.  Half the phases per block and twice the blocks.
+enum Shape { kPlain, kShared, kSplit };
+
+template <int D, bool FINAL, Shape SHAPE>
+__global__ __launch_bounds__((kWaves * 64), (SHAPE == kShared ? 4 : 2)) void sfa_fwd_bf16_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ k, const bf16 *__restrict__ v,
     bf16 *__restrict__ o, float *__restrict__ lse, SfaGeom g)
 {
+    constexpr bool SPLIT = SHAPE == kSplit;
     constexpr int KS = D / 16;  // MFMA k-steps over the head dim
     constexpr int DB = D / 32;  // 32-wide head-dim blocks of O
     using T = Tile<D>;
     // two-slot K and V rings (tile t in slot t % 2); every slot is an immediate offset
     // from one per-lane address
-    __shared__ __attribute__((aligned(1024))) char ks[2][T::BYTES];
-    __shared__ __attribute__((aligned(1024))) char vs[2][T::BYTES];
+    // (split: one pair of rings per group, which at the end hold group B's part: per wave and
+    // lane 16 DB accumulators, the reference and the row sum)
+    constexpr int NR = SPLIT ? 2 : 1;
+    constexpr int BM = SPLIT ? kBM / 2 : kBM;
+    __shared__ __attribute__((aligned(1024))) char kv[NR][4][T::BYTES];
+    static_assert(!SPLIT || sizeof(kv) >= 4 * (16 * DB + 2) * 64 * sizeof(float), "group B's part must fit in the rings");
 
-    const int ntiles = (g.qlen + kBM - 1) / kBM;
+    const int ntiles = (g.qlen + BM - 1) / BM;
     const int nprob = g.B * g.Hq * g.streams;
     int prob, tile;
     decode_tile(blockIdx.x, nprob, ntiles, prob, tile);
@@ -71,24 +83,32 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches
     const int group = wave >> 2;  // 0: A, 1: B (one wave of each per SIMD)
     const int l32 = lane & 31, hi = lane >> 5;
-    const int q0 = tile * kBM;
+    char (&ks)[2][T::BYTES] = *reinterpret_cast<char (*)[2][T::BYTES]>(kv[SPLIT ? group : 0]);
+    char (&vs)[2][T::BYTES] = *reinterpret_cast<char (*)[2][T::BYTES]>(kv[SPLIT ? group : 0] + 2);
+    const int q0 = tile * BM;
+    constexpr int RW = BM / 32;                // waves that share the block's rows
+    const int rw = SPLIT ? wave & 3 : wave;    // my place among them
+    constexpr int TS = SPLIT ? 2 : 1;          // key tiles between my tiles
+    const int t0 = SPLIT ? group : 0;          // my first key tile of the block
     // This wave's 32 query rows: 32 consecutive rows, or, in final-stream layers (whose
-    // queries advance n key positions per row), rows wave, wave + 8, ... of the block,
-    // so that all eight waves reach (about) the same last key tile.
+    // queries advance n key positions per row), rows rw, rw + RW, ... of the block,
+    // so that all waves reach (about) the same last key tile.
     auto P = [&](int i) __attribute__((always_inline)) { return FINAL ? qpos(g, i) : i; };
-    const int row = FINAL ? q0 + wave + 8 * l32 : q0 + wave * 32 + l32;
-    const int wrow_min = FINAL ? q0 + wave : q0 + wave * 32;
-    const int wrow_max = FINAL ? wrow_min + 8 * 31 : wrow_min + 31;
+    const int row = FINAL ? q0 + rw + RW * l32 : q0 + rw * 32 + l32;
+    const int wrow_min = FINAL ? q0 + rw : q0 + rw * 32;
+    const int wrow_max = FINAL ? wrow_min + RW * 31 : wrow_min + 31;
 
     // keys of the block: up to the key coordinate of its last query row
-    const int kend = min(g.len, P(min(q0 + kBM, g.qlen) - 1) + 1);
+    const int kend = min(g.len, P(min(q0 + BM, g.qlen) - 1) + 1);
     const int nkt = (kend + kRows - 1) / kRows;
     // Tiles are numbered from jf, the first one holding a key that a row of this
-    // workgroup sees (0 unless the layer is local); t below is relative to jf.
+    // workgroup sees (0 unless the layer is local); t below counts my tiles from there:
+    // tile t is key tile jf + t0 + t TS.
     const int jf = max(0, P(q0) - g.window + 1) / kRows;
-    const int ntl = nkt - jf;
-    // last tile with keys this wave sees
-    const int jlast = min(nkt - 1, P(wrow_max) / kRows) - jf;
+    const int ntl = (nkt - jf + TS - 1) / TS;
+    // last tile with keys this wave sees (split: group B may have none, -1)
+    const int jlast = (min(nkt - 1, P(wrow_max) / kRows) - jf - t0 + TS) / TS - 1;
+    auto key0 = [&](int t) __attribute__((always_inline)) { return (jf + t0 + t * TS) * kRows; };
 
     // this lane's query row as the B operand of S^T = K Q^T
     bf16x8 qr[KS];
@@ -100,8 +120,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     }
 
     // per-lane address parts (K and V share the row layout)
-    const bool loader = wave >= kWaves - kLoaders;  // the waves of group B
-    const int lw = loader ? wave - (kWaves - kLoaders) : 0;
+    const bool loader = SPLIT || wave >= kWaves - kLoaders;  // the waves of group B, or of each
+    const int lw = loader ? wave & (kLoaders - 1) : 0;
     const auto dma = T::template dma_plan<kLoaders>(kbase0, kstride, lw, lane);
     uint32_t kro[KS], vto[DB][2];
     T::row_offsets(l32, hi, kro);
@@ -112,9 +132,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     auto issue = [&](int t) __attribute__((always_inline)) {
         if (loader) {
             if (t + 2 < ntl)
-                T::load(ks[t & 1], rk, dma, (uint32_t)((jf + t + 2) * kRows) * kstride, lw);
+                T::load(ks[t & 1], rk, dma, (uint32_t)key0(t + 2) * kstride, lw);
             if (t + 1 < ntl)
-                T::load(vs[(t + 1) & 1], rv, dma, (uint32_t)((jf + t + 1) * kRows) * kstride, lw);
+                T::load(vs[(t + 1) & 1], rv, dma, (uint32_t)key0(t + 1) * kstride, lw);
         }
     };
 
@@ -131,7 +151,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     // the tile holds keys past this wave's first row (diagonal) or, in a local layer,
     // keys at least a window before its last row
     auto needs_mask = [&](int t) __attribute__((always_inline)) {
-        const int kb = (jf + t) * kRows;
+        const int kb = key0(t);
         return kb + kRows - 1 > P(wrow_min) || kb <= P(wrow_max) - g.window;
     };
 
@@ -150,7 +170,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
                 // key = kb + c with c = mb*32 + 8*(r/4) + r%4 + 4*hi; masked if key > row
                 // or row - key >= window, compared against a per-lane limit so the
                 // per-element constants stay immediates
-                const int lim = P(row) - 4 * hi - (jf + t + 1) * kRows;
+                const int lim = P(row) - 4 * hi - key0(t + 1);
                 const int lo = lim - g.window;
                 f32x16 bias[2];
 #pragma unroll
@@ -228,9 +248,9 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
 
     // Prologue: K of tiles 0, 1 and V of tile 0 resident (and the query row).
     if (loader) {
-        T::load(ks[0], rk, dma, (uint32_t)(jf * kRows) * kstride, lw);
-        if (ntl > 1) T::load(ks[1], rk, dma, (uint32_t)((jf + 1) * kRows) * kstride, lw);
-        T::load(vs[0], rv, dma, (uint32_t)(jf * kRows) * kstride, lw);
+        T::load(ks[0], rk, dma, (uint32_t)key0(0) * kstride, lw);
+        if (ntl > 1) T::load(ks[1], rk, dma, (uint32_t)key0(1) * kstride, lw);
+        T::load(vs[0], rv, dma, (uint32_t)key0(0) * kstride, lw);
     }
     wait_vmcnt_le(0);
     lds_barrier();
@@ -254,53 +274,82 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     int nb = 0;  // barriers passed
     auto bar = [&]() __attribute__((always_inline)) { lds_barrier(); ++nb; };
     if (group == 1) bar();
-    mfma_phase(-1, Tr{}, F{}, Z{}, Z{});
-    bar();
-    int t = 0;
-    for (; t + 1 < jlast; t += 2) {
+    if (!SPLIT || jlast >= 0) {
+        mfma_phase(-1, Tr{}, F{}, Z{}, Z{});
+        bar();
+        int t = 0;
+        for (; t + 1 < jlast; t += 2) {
+            vector_phase();
+            issue(t);
+            bar();
+            mfma_phase(t, Tr{}, Tr{}, O{}, Z{});
+            if (loader) wait_vmcnt_le(0);
+            bar();
+            vector_phase();
+            issue(t + 1);
+            bar();
+            mfma_phase(t + 1, Tr{}, Tr{}, Z{}, O{});
+            if (loader) wait_vmcnt_le(0);
+            bar();
+        }
+        if (t < jlast) {  // t even
+            vector_phase();
+            issue(t);
+            bar();
+            mfma_phase(t, Tr{}, Tr{}, O{}, Z{});
+            if (loader) wait_vmcnt_le(0);
+            bar();
+            ++t;
+        }
+        // t == jlast: last softmax and P V product
         vector_phase();
         issue(t);
         bar();
-        mfma_phase(t, Tr{}, Tr{}, O{}, Z{});
+        if (t & 1)
+            mfma_phase(t, F{}, Tr{}, Z{}, O{});
+        else
+            mfma_phase(t, F{}, Tr{}, Z{}, Z{});
         if (loader) wait_vmcnt_le(0);
         bar();
-        vector_phase();
-        issue(t + 1);
-        bar();
-        mfma_phase(t + 1, Tr{}, Tr{}, Z{}, O{});
-        if (loader) wait_vmcnt_le(0);
+    } else {
         bar();
     }
-    if (t < jlast) {  // t even
-        vector_phase();
-        issue(t);
-        bar();
-        mfma_phase(t, Tr{}, Tr{}, O{}, Z{});
-        if (loader) wait_vmcnt_le(0);
-        bar();
-        ++t;
-    }
-    // t == jlast: last softmax and P V product
-    vector_phase();
-    issue(t);
-    bar();
-    if (t & 1)
-        mfma_phase(t, F{}, Tr{}, Z{}, O{});
-    else
-        mfma_phase(t, F{}, Tr{}, Z{}, Z{});
-    if (loader) wait_vmcnt_le(0);
-    bar();
     while (nb < 2 * ntl + 2) {  // idle: past this wave's last tile
         if (loader) {
-            if ((nb & 1) == 0)
-                issue((nb - 2) >> 1);  // barrier 2t+2 ends the vector phase of tile t
+            const int ph = nb - group - 1;  // 2t: the vector phase of tile t, 2t + 1: its matrix phase
+            if ((ph & 1) == 0)
+                issue(ph >> 1);
             else
-                wait_vmcnt_le(0);      // barrier 2t+3 ends its matrix phase
+                wait_vmcnt_le(0);
         }
         bar();
     }
 
-    const float l = sum_xor32(lsum0 + lsum1);
+    float l = sum_xor32(lsum0 + lsum1);
+    if constexpr (SPLIT) {
+        // every wave has passed the last barrier: the rings are free
+        mfma_settle();
+        float *part = reinterpret_cast<float *>(kv) + rw * (16 * DB + 2) * 64 + lane;
+        if (group == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part[(db * 16 + r) * 64] = oacc[db][r];
+            part[16 * DB * 64] = m2;
+            part[(16 * DB + 1) * 64] = l;
+        }
+        lds_barrier();
+        if (group == 1) return;
+        // a group without a visible key has reference -inf, sum 0 and zero accumulators
+        const float mb = part[16 * DB * 64], mt = fmaxf(m2, mb);
+        const float wa = m2 == mt ? 1.f : fast_exp2(m2 - mt), wb = mb == mt ? 1.f : fast_exp2(mb - mt);
+        l = l * wa + part[(16 * DB + 1) * 64] * wb;
+        m2 = mt;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][r] = oacc[db][r] * wa + part[(db * 16 + r) * 64] * wb;
+    }
     if (row < g.qlen) {
         const float inv = 1.f / l;
         const uint32_t obase = qbase + (uint32_t)row * qstride;
@@ -320,24 +369,48 @@ __global__ __launch_bounds__(kWaves * 64, 1) void sfa_fwd_bf16_kernel(
     }
 }
 
+// The block shape for a grid of `wgs` 256-row blocks (256 CUs):
+//   up to kSplitMax of them, the split one: it halves the longest block where CUs would idle
+//     (D=128, 32 blocks of 2000 rows: 31 -> 22 us; 96 blocks of 6124 rows: 127 -> 80; 192
+//     blocks at D=64: 30 -> 22; but 256 short blocks, L=302: 20 -> 24);
+//   at D=64 above kPlainMax, two workgroups per CU: each one's softmax and barriers overlap the
+//     other's MFMAs (768 blocks: 115 -> 101 us, 9216 blocks: 1116 -> 985), while a grid that
+//     would be resident at once then puts long causal blocks on one CU (288 blocks: 80 -> 87).
+constexpr int kSplitMax = 192;
+constexpr int kPlainMax = 512;
+Shape fwd_shape(int D, int64_t wgs)
+{
+    return wgs <= kSplitMax ? kSplit : D == 64 && wgs > kPlainMax ? kShared : kPlain;
+}
+
 }  // namespace
 
 hipError_t launch_fwd_bf16(const void *q, const void *k, const void *v, void *o, float *lse,
                            const SfaGeom &g, hipStream_t s)
 {
-    const int ntiles = (g.qlen + kBM - 1) / kBM;
     const int nprob = g.B * g.Hq * g.streams;
-    const dim3 grid(ntiles * nprob), block(kWaves * 64);
+    const int wgs = (g.qlen + kBM - 1) / kBM * nprob;
+    const Shape shape = fwd_shape(g.D, wgs);
+    const dim3 grid(shape == kSplit ? (g.qlen + kBM / 2 - 1) / (kBM / 2) * nprob : wgs), block(kWaves * 64);
     const bf16 *qq = static_cast<const bf16 *>(q), *kk = static_cast<const bf16 *>(k),
                *vv = static_cast<const bf16 *>(v);
     bf16 *oo = static_cast<bf16 *>(o);
     auto launch = [&](auto dk, const char *name) {
         constexpr int DD = decltype(dk)::value;
         timing_before(name, s);
+        auto go = [&](auto fin) {
+            constexpr bool FIN = decltype(fin)::value;
+            if (shape == kSplit)
+                sfa_fwd_bf16_kernel<DD, FIN, kSplit><<<grid, block, 0, s>>>(qq, kk, vv, oo, lse, g);
+            else if (DD == 64 && shape == kShared)
+                sfa_fwd_bf16_kernel<DD, FIN, DD == 64 ? kShared : kPlain><<<grid, block, 0, s>>>(qq, kk, vv, oo, lse, g);
+            else
+                sfa_fwd_bf16_kernel<DD, FIN, kPlain><<<grid, block, 0, s>>>(qq, kk, vv, oo, lse, g);
+        };
         if (g.strided_waves)
-            sfa_fwd_bf16_kernel<DD, true><<<grid, block, 0, s>>>(qq, kk, vv, oo, lse, g);
+            go(std::true_type{});
         else
-            sfa_fwd_bf16_kernel<DD, false><<<grid, block, 0, s>>>(qq, kk, vv, oo, lse, g);
+            go(std::false_type{});
     };
     const bool f = g.strided_waves;
     switch (g.D) {
