@@ -20,7 +20,7 @@
 //          per wave, one row per lane) and streams the dS tiles and key rows at or
 //          below the diagonal through an LDS ring (32 keys x 2 stages, several
 //          workgroups per CU, unless that would make the whole grid resident at
-//          once; then 64 keys x 3 stages), dQ^T += K^T dS^T with
+//          once; then 64 keys x 3 stages; small grids 128-row blocks, see below), dQ^T += K^T dS^T with
 //          both operands read transposed from LDS.  No S or dP is recomputed, so this
 //          pass is bound by the dS reads from HBM.
 // All tiles move HBM -> LDS through direct-to-LDS buffer loads.
@@ -33,8 +33,8 @@ namespace hd {
 
 namespace {
 
-constexpr int kKeysPerWg = 128;  // dK/dV: 4 key groups of 32, each shared by 2 waves
-constexpr int kDkdvWaves = 8;
+// dK/dV: KW key groups of 32 per workgroup (KW = 4 or 2), each shared by 2 waves
+constexpr int kMaxKeysPerWg = 128;
 constexpr int kDqWaves = 8;
 constexpr int kRowsPerWg = kDqWaves * 32;  // dQ: 8 waves (two per SIMD) x 32 rows
 static_assert(kRowsPerWg == kBandUnit * kDsRows, "a query band unit is one dQ workgroup's rows");
@@ -94,36 +94,38 @@ __global__ __launch_bounds__(256) void bwd_stats_bf16_kernel(const bf16 *__restr
     }
 }
 
-template <int D>
-__global__ __launch_bounds__(kDkdvWaves * 64, 1) void sfa_dkdv_bf16_kernel(
+template <int D, int KW>
+__global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ k, const bf16 *__restrict__ v,
     const bf16 *__restrict__ dO, const float *__restrict__ delta, const float *__restrict__ lse2,
     bf16 *__restrict__ dk, bf16 *__restrict__ dv, bf16 *__restrict__ ds, int64_t ds_tiles, SfaGeom g,
     QBand bd, int nsplit, float *__restrict__ split, SplitOrder order)
 {
     constexpr int DB = D / 32, KS = D / 16;
+    constexpr int kKeysPerWg = 32 * KW, kDkdvWaves = 2 * KW;
+    constexpr int SUB = kMaxKeysPerWg / kKeysPerWg;  // workgroups per 128-key tile
+    static_assert(kMaxKeysPerWg == kDsKeys && kKeysPerWg % kRows == 0, "a workgroup's keys lie in one dS tile");
     using T = Tile<D>;
     constexpr int STAGE = 2 * T::BYTES + 2 * kRows * 4;       // Q | dO | lse2 | delta
     constexpr int KV = 2 * (kKeysPerWg / kRows) * T::BYTES;  // K tiles | V tiles
     constexpr int LDS = 2 * STAGE + KV;
-    static_assert(2 * (kDkdvWaves / 2) * DB * 16 * 64 * 4 <= LDS, "partials must fit in LDS");
+    static_assert(2 * KW * DB * 16 * 64 * 4 <= LDS, "partials must fit in LDS");
     __shared__ __attribute__((aligned(1024))) char smem[LDS];
     char *const kvt = smem + 2 * STAGE;
 
-    const int nkt = (g.len + kKeysPerWg - 1) / kKeysPerWg;
+    const int nkt = (g.len + kMaxKeysPerWg - 1) / kMaxKeysPerWg;  // 128-key tiles
     const int nprob = g.B * g.Hkv * g.streams;
     // work item: a key tile's whole sweep, or with split sweeps (nsplit > 0) one half of
     // the sweep of one of the first nsplit key tiles, the items taken longest first
-    int prob, ktile, half;
+    // (the SUB workgroups of a 128-key tile follow one another)
+    int prob, rank, ktile, half = -1;
+    decode_key_tile(blockIdx.x, nprob, (nkt + nsplit) * SUB, prob, rank);
+    const int sub = rank % SUB;
+    ktile = rank / SUB;
     if (nsplit > 0) {
-        int rank;
-        decode_key_tile(blockIdx.x, nprob, nkt + nsplit, prob, rank);
-        const int code = order.item[rank];
+        const int code = order.item[ktile];
         ktile = code >> 2;
         half = (code & 3) - 1;  // -1: the whole sweep, 0: its later half, 1: its earlier half
-    } else {
-        decode_key_tile(blockIdx.x, nprob, nkt, prob, ktile);
-        half = -1;
     }
     const int s = prob % g.streams;
     const int hk = (prob / g.streams) % g.Hkv;
@@ -141,13 +143,14 @@ __global__ __launch_bounds__(kDkdvWaves * 64, 1) void sfa_dkdv_bf16_kernel(
     const uint32_t kstride = (uint32_t)g.rowmul * g.Hkv * D * 2;
     const uint32_t kbase = (uint32_t)(s * g.Hkv + hk) * D * 2;
 
-    // waves w and w + 4 own the same 32 keys; w takes query rows 0..31 of every
-    // 64-row tile and w + 4 rows 32..63; their dK/dV partials are summed at the end
+    // waves w and w + KW own the same 32 keys; w takes query rows 0..31 of every
+    // 64-row tile and w + KW rows 32..63; their dK/dV partials are summed at the end
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches
     const int l32 = lane & 31, hi = lane >> 5;
-    const int kw = wave & 3, qb = wave >> 2;
-    const int k0 = ktile * kKeysPerWg;
+    const int kw = wave % KW, qb = wave / KW;
+    const int k0 = ktile * kMaxKeysPerWg + sub * kKeysPerWg;
+    if (SUB > 1 && k0 >= g.len) return;  // the last tile's upper half may hold no key
     const int kw0 = k0 + kw * 32;
     const int key = kw0 + l32;
 
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(kDkdvWaves * 64, 1) void sfa_dkdv_bf16_kernel(
         const int64_t prob_q = ((int64_t)b * g.Hq + hk * g.G + gi) * g.streams + s;
         return ds + prob_q * ds_tiles * (kDsTileBytes / 2);
     };
-    const uint32_t dsoff = (uint32_t)(qb * kDsKeys + kw * 32 + l32) * 64 + hi * 32;
+    const uint32_t dsoff = (uint32_t)(qb * kDsKeys + sub * kKeysPerWg + kw * 32 + l32) * 64 + hi * 32;
     const char *ktl = kvt + (kw >> 1) * T::BYTES;                              // tile of my keys
     const char *vtl = kvt + (kKeysPerWg / kRows + (kw >> 1)) * T::BYTES;
     const int krow = (kw & 1) * 32 + l32;                                      // my key's row there
@@ -373,8 +376,8 @@ __global__ __launch_bounds__(kDkdvWaves * 64, 1) void sfa_dkdv_bf16_kernel(
         if (it + 1 < iters) step(it + 1, std::integral_constant<int, 1>{});
     }
 
-    // sum the two query halves: waves 4..7 park their partials in LDS (one 16-byte
-    // slot per lane and register quad), waves 0..3 add them and write dK/dV
+    // sum the two query halves: waves KW.. park their partials in LDS (one 16-byte
+    // slot per lane and register quad), waves 0..KW-1 add them and write dK/dV
     f32x4 *park = reinterpret_cast<f32x4 *>(smem) + kw * (2 * DB * 4 * 64);
     if (qb == 1) {
 #pragma unroll
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(kDkdvWaves * 64, 1) void sfa_dkdv_bf16_kernel(
     __syncthreads();
     if (half >= 0 && qb == 0 && key < g.len) {
         // one half of a split sweep: fp32 sums [half][dK, dV][problem][key][D]
-        const size_t slice = (size_t)nsplit * kKeysPerWg * D;
+        const size_t slice = (size_t)nsplit * kMaxKeysPerWg * D;
         float *pk = split + ((size_t)(half * 2) * nprob + prob) * slice + (size_t)key * D;
         float *pv = split + ((size_t)(half * 2 + 1) * nprob + prob) * slice + (size_t)key * D;
 #pragma unroll
@@ -449,7 +452,7 @@ __global__ __launch_bounds__(256) void dkdv_split_combine_kernel(const float *__
                                                                  bf16 *__restrict__ dv, SfaGeom g)
 {
     const int nprob = g.B * g.Hkv * g.streams;
-    const int keys = nsplit * kKeysPerWg;
+    const int keys = nsplit * kMaxKeysPerWg;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)nprob * keys * (D / 4)) return;
     const int d0 = (int)(idx % (D / 4)) * 4;
@@ -474,7 +477,12 @@ __global__ __launch_bounds__(256) void dkdv_split_combine_kernel(const float *__
 // workgroups share a CU and each one's loads overlap the other's MFMAs; <64, 3> takes
 // 144 KB, one workgroup per CU, and wins when the whole grid would otherwise be resident
 // at once (the dispatcher then cannot pair long causal row blocks with short ones).
-template <int D, int KK, int S>
+//
+// SPLIT (small grids): a workgroup owns 128 rows, waves w and w + 4 the same 32, and the two
+// groups of four waves take every second key step each, through rings of their own; the
+// second group's sums are added through LDS at the end.  Half the steps and twice the
+// workgroups.
+template <int D, int KK, int S, bool SPLIT = false>
 __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
     const bf16 *__restrict__ k, const bf16 *__restrict__ ds, bf16 *__restrict__ dq, SfaGeom g,
     int64_t ds_tiles, QBand bd)
@@ -484,12 +492,16 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
     using T = Tile<D, KK>;
     // a wave's dS slab of one step: KK keys x 32 queries, 64 bytes per key
     constexpr int kSlab = KK * 64;
-    constexpr int kStage = T::BYTES + kDqWaves * kSlab;  // K rows | dS slabs
-    static_assert(S * kStage <= 160 * 1024, "the ring must fit in LDS");
-    __shared__ __attribute__((aligned(1024))) char smem[S][kStage];
+    constexpr int NG = SPLIT ? 2 : 1;                  // groups of waves with a ring of their own
+    constexpr int GW = kDqWaves / NG;                  // waves per group
+    constexpr int kRowsPerWg = GW * 32;
+    constexpr int kStage = T::BYTES + GW * kSlab;      // K rows | dS slabs
+    static_assert(NG * S * kStage <= 160 * 1024, "the rings must fit in LDS");
+    static_assert(!SPLIT || NG * S * kStage >= GW * DB * 16 * 64 * 4, "the second group's sums must fit in the rings");
+    __shared__ __attribute__((aligned(1024))) char rings[NG][S][kStage];
 
-    // the 256-row blocks of this query band (its first tile is a multiple of four)
-    const int rb_lo = bd.qt_lo / kBandUnit;
+    // the row blocks of this query band (its first tile is a multiple of four)
+    const int rb_lo = bd.qt_lo * kDsRows / kRowsPerWg;
     const int ntiles = (min(bd.qt_hi * kDsRows, g.qlen) + kRowsPerWg - 1) / kRowsPerWg - rb_lo;
     const int nprob = g.B * g.Hq * g.streams;
     int prob, tile;
@@ -511,11 +523,13 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches
     const int l32 = lane & 31, hi = lane >> 5;
+    const int group = SPLIT ? wave / GW : 0, gwave = wave % GW;
+    char (&smem)[S][kStage] = rings[group];
     const int q0 = tile * kRowsPerWg;
     // MFMA column l32 holds the query at position l32 of the dS tile layout
-    const int row = q0 + wave * 32 + ds_query_at(l32);
-    const int wrow_min = q0 + wave * 32, wrow_max = wrow_min + 31;
-    // my rows are half (wave & 1) of dS query tile qt
+    const int row = q0 + gwave * 32 + ds_query_at(l32);
+    const int wrow_min = q0 + gwave * 32, wrow_max = wrow_min + 31;
+    // my rows are half (gwave & 1) of dS query tile qt
     const int qt = wrow_min / kDsRows;
     const int band = ds_band(g);
     const int kt_lo = ds_kt_lo(g, qt);
@@ -526,6 +540,8 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
     const int nkt = (kend + KK - 1) / KK;
     // first key step any row of the workgroup sees (0 unless the layer is local)
     const int jf = max(0, qpos(g, q0) - g.window + 1) / KK;
+    // my group's steps: jg, jg + NG, .. (the groups pass the same number of barriers)
+    const int jg = jf + group, steps = (nkt - jf + NG - 1) / NG;
     // wave-uniform: key step j holds a key that a row of this wave sees (then the dS
     // tile that holds it exists)
     auto active = [&](int j) __attribute__((always_inline)) {
@@ -534,26 +550,26 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
                qpos(g, wrow_min) - (kb0 + KK - 1) < g.window;
     };
     constexpr int kSteps = kDsKeys / KK;  // key steps per dS tile
-    const int kloads = loads_per_wave(T::INSTR, wave, kDqWaves);
+    const int kloads = loads_per_wave(T::INSTR, gwave, GW);
     // this wave's loads of step j (in-order completion makes counts enough to wait on)
     auto nloads = [&](int j) __attribute__((always_inline)) {
         return j < nkt ? kloads + (active(j) ? kSlab / 1024 : 0) : 0;
     };
-    static_assert((S - 2) * (T::INSTR / kDqWaves + 1 + kSlab / 1024) <= 15,
+    static_assert((S - 2) * (T::INSTR / GW + 1 + kSlab / 1024) <= 15,
                   "outstanding loads must fit the vmcnt wait");
     // K rows of a step: per-lane offsets computed once; rows past the end of the
     // problem lie past the end of the batch's buffer range and load zeros
-    const auto kplan = T::template dma_plan<kDqWaves>(kbase, kstride, wave, lane);
+    const auto kplan = T::template dma_plan<GW>(kbase, kstride, gwave, lane);
     auto issue = [&](int j) __attribute__((always_inline)) {
         if (j >= nkt) return;
-        char *st = smem[(j - jf) % S];
-        T::load(st, rk, kplan, (uint32_t)(j * KK) * kstride, wave);
+        char *st = smem[(j - jg) / NG % S];
+        T::load(st, rk, kplan, (uint32_t)(j * KK) * kstride, gwave);
         if (active(j)) {
             const int64_t t = ds_tile_index(band, kt_lo, qt, j / kSteps) - bd.ds_base;
             const rsrc_t rt = make_rsrc(ds_prob + t * (kDsTileBytes / 2), kDsTileBytes);
-            char *slab = st + T::BYTES + wave * kSlab;
+            char *slab = st + T::BYTES + gwave * kSlab;
             const uint32_t off =
-                (uint32_t)((wave & 1) * kDsKeys + (j % kSteps) * KK) * 64 + lane * 16;
+                (uint32_t)((gwave & 1) * kDsKeys + (j % kSteps) * KK) * 64 + lane * 16;
 #pragma unroll
             for (int oc = 0; oc < kSlab / 1024; ++oc)
                 dma_lds16_nt(rt, slab + oc * 1024, off + oc * 1024);
@@ -574,22 +590,23 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
 #pragma unroll
     for (int db = 0; db < DB; ++db) adq[db] = f32x16{};
 
-    // steps jf .. jf+S-2 in flight; step j's stage is free again once every wave has
-    // passed the barrier that ends step j - 1
+    // the first S-1 steps in flight; a step's stage is free again once every wave has
+    // passed the barrier that ends the step before it
 #pragma unroll
-    for (int i = 0; i < S - 1; ++i) issue(jf + i);
+    for (int i = 0; i < S - 1; ++i) issue(jg + i * NG);
     {
         int pend = 0;
 #pragma unroll
-        for (int i = 1; i < S - 1; ++i) pend += nloads(jf + i);
+        for (int i = 1; i < S - 1; ++i) pend += nloads(jg + i * NG);
         wait_vmcnt_le(pend);
     }
     lds_barrier();
-    for (int j = jf; j < nkt; ++j) {
-        issue(j + S - 1);
-        if (active(j)) {
-            const char *kt = smem[(j - jf) % S];
-            const char *slab = kt + T::BYTES + wave * kSlab;
+    for (int i = 0; i < steps; ++i) {
+        const int j = jg + i * NG;
+        issue(j + (S - 1) * NG);
+        if ((!SPLIT || j < nkt) && active(j)) {
+            const char *kt = smem[i % S];
+            const char *slab = kt + T::BYTES + gwave * kSlab;
 #pragma unroll
             for (int kk = 0; kk < KK / 16; ++kk) {
                 const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -602,15 +619,31 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
                 for (int db = 0; db < DB; ++db) adq[db] = mfma32(T::tr_at(kt, kto[db], kk), bop, adq[db]);
             }
         }
-        // step j + 1 has landed once at most the loads of steps j + 2 .. j + S - 1 are
+        // the next step has landed once at most the loads of the S - 2 steps after it are
         // outstanding
         {
             int pend = 0;
 #pragma unroll
-            for (int i = 2; i < S; ++i) pend += nloads(j + i);
+            for (int x = 2; x < S; ++x) pend += nloads(j + x * NG);
             wait_vmcnt_le(pend);
         }
         lds_barrier();
+    }
+    if constexpr (SPLIT) {
+        mfma_settle();
+        float *part = reinterpret_cast<float *>(rings) + gwave * (DB * 16 * 64) + lane;
+        if (group == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part[(db * 16 + r) * 64] = adq[db][r];
+        }
+        lds_barrier();
+        if (group == 1) return;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) adq[db][r] += part[(db * 16 + r) * 64];
     }
 
     if (row < g.qlen) {
@@ -626,6 +659,16 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
             }
     }
 }
+
+// Small grids.  dK/dV with at most kNarrowItems work items of 128 keys takes workgroups of 64
+// keys and four waves: twice as many, each with its SIMDs to itself (96 items at D=128: 42 ->
+// 37 us, 24 items 57 -> 50; but 176 items 28 -> 32, which no longer fit one per CU).  dQ with
+// at most kDqSplitMax 256-row blocks takes 128-row blocks whose key steps the wave groups
+// split (32 blocks at D=128, N=1000: 26 -> 19 us; 64 of L=1000: 26 -> 19; 264 final-stream blocks
+// 28 -> 30).  The choice for dQ looks at all of the problem's rows, not at a query
+// band's, so that dQ does not depend on the workspace.
+constexpr int kNarrowItems = 128;
+constexpr int kDqSplitMax = 192;
 
 template <int D>
 hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o,
@@ -655,7 +698,7 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
         return e;
 
-    const int nkt = (g.len + kKeysPerWg - 1) / kKeysPerWg;
+    const int nkt = (g.len + kMaxKeysPerWg - 1) / kMaxKeysPerWg;
     const int nqt = (g.qlen + kDsRows - 1) / kDsRows;
     const int band = ds_band(g);
     const int64_t nprob_q = (int64_t)g.B * g.Hq * g.streams;
@@ -681,13 +724,18 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         SplitOrder order;
         if (nsplit > 0) order = dkdv_split_order(g, nsplit);
         timing_before(dkdv_name, s);
-        sfa_dkdv_bf16_kernel<D><<<(nkt + nsplit) * g.B * g.Hkv * g.streams, kDkdvWaves * 64, 0, s>>>(
-            q, k, v, dO, delta, lse2, dk, dv, ds, band_tiles, g, bd, nsplit, split, order);
+        const int items = (nkt + nsplit) * g.B * g.Hkv * g.streams;
+        if (items <= kNarrowItems)
+            sfa_dkdv_bf16_kernel<D, 2><<<items * 2, 256, 0, s>>>(q, k, v, dO, delta, lse2, dk, dv, ds, band_tiles,
+                                                                 g, bd, nsplit, split, order);
+        else
+            sfa_dkdv_bf16_kernel<D, 4><<<items, 512, 0, s>>>(q, k, v, dO, delta, lse2, dk, dv, ds, band_tiles,
+                                                             g, bd, nsplit, split, order);
         e = hipGetLastError();
         timing_after(s);
         if (e != hipSuccess) return e;
         if (nsplit > 0) {
-            const int64_t n4 = (int64_t)g.B * g.Hkv * g.streams * nsplit * kKeysPerWg * (D / 4);
+            const int64_t n4 = (int64_t)g.B * g.Hkv * g.streams * nsplit * kMaxKeysPerWg * (D / 4);
             timing_before(D == 32 ? "sfa_dkdv_split_combine_d32"
                                   : D == 64 ? "sfa_dkdv_split_combine_d64" : "sfa_dkdv_split_combine_d128",
                           s);
@@ -698,8 +746,12 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         }
         const int nrb = (min(qb * kDsRows, g.qlen) + kRowsPerWg - 1) / kRowsPerWg - qa / kBandUnit;
         const int64_t wgs = nrb * nprob_q;
+        const bool dq_split = (int64_t)((g.qlen + kRowsPerWg - 1) / kRowsPerWg) * nprob_q <= kDqSplitMax;
         timing_before(dq_name, s);
-        if (wgs > (int64_t)per_cu * cus)
+        if (dq_split) {
+            const int nhb = (min(qb * kDsRows, g.qlen) + kRowsPerWg / 2 - 1) / (kRowsPerWg / 2) - qa / kBandUnit * 2;
+            sfa_dq_bf16_kernel<D, 64, 2, true><<<(unsigned)(nhb * nprob_q), kDqWaves * 64, 0, s>>>(k, ds, dq, g, band_tiles, bd);
+        } else if (wgs > (int64_t)per_cu * cus)
             sfa_dq_bf16_kernel<D, 32, 2><<<(unsigned)wgs, kDqWaves * 64, 0, s>>>(k, ds, dq, g, band_tiles, bd);
         else
             sfa_dq_bf16_kernel<D, 64, 3><<<(unsigned)wgs, kDqWaves * 64, 0, s>>>(k, ds, dq, g, band_tiles, bd);
