@@ -344,16 +344,16 @@ def sfa_backward(q, k, v, o, lse, dO, *, n, mode, scale, window=None, workspace=
     import torch
 
     B, L, Hq, Hkv, D = _shape(q, k, n)
-    dtype = _dtype_code(q, None)
-    if _local(mode, window):
-        need = hd_sfa_bwd_local_workspace_bytes(B, L, n, Hq, Hkv, D, window, dtype)
-    else:
-        need = hd_sfa_bwd_workspace_bytes(B, L, n, Hq, Hkv, D, mode, dtype)
+    local = _local(mode, window)
     if workspace is None:
-        workspace = torch.empty(need if workspace_bytes is None else int(workspace_bytes),
-                                dtype=torch.uint8, device=q.device)
+        if workspace_bytes is None:
+            dtype = _dtype_code(q, None)
+            workspace_bytes = (hd_sfa_bwd_local_workspace_bytes(B, L, n, Hq, Hkv, D, window, dtype)
+                               if local else
+                               hd_sfa_bwd_workspace_bytes(B, L, n, Hq, Hkv, D, mode, dtype))
+        workspace = torch.empty(int(workspace_bytes), dtype=torch.uint8, device=q.device)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-    if _local(mode, window):
+    if local:
         hd_sfa_bwd_local(q, k, v, o, lse, dO, dq, dk, dv, B, L, n, Hq, Hkv, D, window, scale,
                          workspace, workspace.numel(), stream=stream)
     else:
@@ -448,10 +448,11 @@ def sfa_final_backward(q, k, v, o, lse, dO, *, n, scale, window=0, workspace=Non
 
     B, L, Hq, D = q.shape
     Hkv = k.shape[2]
-    need = hd_sfa_bwd_final_workspace_bytes(B, L, n, Hq, Hkv, D, window, _dtype_code(q, None))
     if workspace is None:
-        workspace = torch.empty(need if workspace_bytes is None else int(workspace_bytes),
-                                dtype=torch.uint8, device=q.device)
+        if workspace_bytes is None:
+            workspace_bytes = hd_sfa_bwd_final_workspace_bytes(B, L, n, Hq, Hkv, D, window,
+                                                               _dtype_code(q, None))
+        workspace = torch.empty(int(workspace_bytes), dtype=torch.uint8, device=q.device)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     hd_sfa_bwd_final(q, k, v, o, lse, dO, dq, dk, dv, B, L, n, Hq, Hkv, D, window, scale,
                      workspace, workspace.numel(), stream=stream)
@@ -468,8 +469,8 @@ def sfa_decode(q, k_cache, v_cache, ctx_tokens, *, max_ctx, mode, scale, window=
     B, n, Hq, D = q.shape
     Lcap = k_cache.shape[1] // n
     Hkv = k_cache.shape[2]
-    need = hd_sfa_decode_workspace_bytes(B, Lcap, n, Hq, Hkv, D, mode, window, max_ctx)
     if workspace is None:
+        need = hd_sfa_decode_workspace_bytes(B, Lcap, n, Hq, Hkv, D, mode, window, max_ctx)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
     o = torch.empty_like(q)
     lse = torch.empty((B, Hq, n), dtype=torch.float32, device=q.device)

@@ -4,6 +4,7 @@
 // the kernels then run on the caller's stream.  No allocation, no synchronisation.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -81,7 +82,7 @@ struct TimingRecord {
 };
 
 std::mutex g_tmu;
-bool g_timing = false;
+std::atomic<bool> g_timing{false};
 std::string g_tfilter;  // time only kernels whose name starts with this (empty: all)
 std::vector<hipEvent_t> g_pool;
 std::vector<TimingRecord> g_records;
@@ -105,6 +106,11 @@ namespace hd {
 
 void timing_before(const char *name, hipStream_t s)
 {
+    // off (the usual case): no lock; g_open stays -1
+    if (!g_timing.load(std::memory_order_acquire)) {
+        g_open = -1;
+        return;
+    }
     std::lock_guard<std::mutex> lk(g_tmu);
     g_open = -1;
     if (!g_timing || strncmp(name, g_tfilter.c_str(), g_tfilter.size()) != 0) return;
@@ -117,8 +123,8 @@ void timing_before(const char *name, hipStream_t s)
 
 void timing_after(hipStream_t s)
 {
+    if (g_open < 0) return;  // thread-local
     std::lock_guard<std::mutex> lk(g_tmu);
-    if (g_open < 0) return;
     (void)hipEventRecord(g_records[g_open].stop, s);
     g_open = -1;
 }
