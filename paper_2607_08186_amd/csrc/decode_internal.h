@@ -17,42 +17,54 @@ struct DecGeom {
     int nsplit;        // workgroups per problem (for the longest context), at most nchunk
     int problems;      // B * Hkv * ngc (* n for intra-stream layers)
     int nslot;         // query slots per problem: gchunk (intra-stream) or n * gchunk
+    int waves;         // per workgroup of the partial kernel: 2, 4 or 8
+    int single;        // cached rows up to which one workgroup takes a whole problem
 };
 
-// Rows per workgroup of a problem with `rows` cached rows to read.  Up to kDecSingle rows one
-// workgroup takes them all, with no combine pass (300 rows of 32 problems at D=128: 13.0
-// against 14.5 us; 778 rows 16.8 against 14.1).  Beyond, the rows are spread so that all
-// problems together make about as many workgroups as the chip holds at once
-// (kDecTarget at D=128: two per CU), in whole tiles of four waves and at least kDecChunk
-// rows each (the workspace has room for that many partials).  16 sequences x 4096 tokens,
-// n=4, 32/8 heads of 128, full cross-stream: 177 us with 512 workgroups, 192 with 1024, 199
-// with 2048 (more partials, and more prologues that load nothing), 243 with one per 256 rows.
+// Split of a problem's cached rows over workgroups.  Up to `single` rows one workgroup takes
+// them all, with no combine pass.  Beyond, the rows are spread so that all problems
+// together make about as many workgroups as the chip holds at once (kDecTarget at D=128:
+// two per CU), in whole tiles of four waves and at least kDecChunk rows each (the workspace
+// has room for that many partials).  16 sequences x 4096 tokens, n=4, 32/8 heads of 128,
+// full cross-stream: 177 us with 512 workgroups, 192 with 1024, 199 with 2048 (more
+// partials, and more prologues that load nothing), 243 with one per 256 rows.
 constexpr int kDecChunk = 256;
-constexpr int kDecSingle = 384;
 constexpr int kDecTarget = 512;
 __host__ __device__ inline int dec_target(int D) { return kDecTarget * (128 / D); }
-__host__ __device__ inline int dec_split_rows(int problems, int D, int rows)
+__host__ __device__ inline int dec_split_rows(int problems, int D, int single, int rows)
 {
-    if (rows <= kDecSingle) return kDecSingle;
+    if (rows <= single) return single;
     const int target = dec_target(D);
     const int64_t per = ((int64_t)rows * problems + target - 1) / target;
     return per <= kDecChunk ? kDecChunk : (int)((per + 127) / 128 * 128);
 }
 // upper bound of the splits over all sequences of at most `rows` rows
-inline int dec_max_splits(int problems, int D, int rows)
+inline int dec_max_splits(int problems, int D, int single, int rows)
 {
-    if (rows <= kDecSingle) return 1;
+    if (rows <= single) return 1;
     const int by_rows = (rows + kDecChunk - 1) / kDecChunk;
     const int by_target = (dec_target(D) + problems - 1) / problems;
     return by_rows < by_target ? by_rows : by_target;
 }
-// Four waves per workgroup in place of two where that still leaves one workgroup's place per CU:
-// few rows in all, whose latency counts (8 problems x 3112 rows 16.1 against 19.3 us);
-// with more, two workgroups of two waves overlap each other's prologue and merge (32 x 4096
-// rows 20.0 against 22.5, 32 x 8004 rows 35 against 48).
-inline bool dec_wide(int problems, int D, int nsplit)
+
+// Waves per workgroup and `single`, from the most rows that the cache can hold (and not from
+// the bound on this call's contexts, so that a sequence's result does not depend on it):
+//   8 waves, one tile in flight each, where at most one problem per CU has at most 1024
+//     rows: the whole problem in one launch (D=128, launch to launch: 256 problems x 501 rows
+//     22.1 us in 2 splits, 15.5 in one; x 1001 rows 32 and 26.5; 128 x 801 rows 18.6 and
+//     15.9).  With 64 problems or fewer the split's larger grid wins earlier (64 x 516 rows
+//     15.8 and 14.7, 32 x 764 rows 15.1 and 15.6);
+//   4 waves, two tiles in flight each, where that leaves at most one workgroup per CU: few
+//     rows in all, whose latency counts (8 problems x 3112 rows: 16.1 us against 19.3);
+//   2 waves else: two workgroups per CU overlap each other's prologue and merge (32 problems
+//     x 4096 rows 20.0 us against 22.5, 32 x 8004 rows 35 against 48).
+inline void dec_shape(int problems, int D, int cap_rows, int &waves, int &single)
 {
-    return (int64_t)problems * nsplit <= dec_target(D) / 2;
+    const int most = problems <= 64 ? 640 : 1024;
+    const bool few = problems <= 256 && cap_rows <= most;
+    single = few ? most : 384;
+    const int64_t wgs = (int64_t)problems * dec_max_splits(problems, D, single, cap_rows);
+    waves = few ? 8 : wgs <= dec_target(D) / 2 ? 4 : 2;
 }
 
 DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, int window,

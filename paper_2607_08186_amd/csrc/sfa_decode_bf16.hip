@@ -23,6 +23,7 @@
 // Measured at 16 x 4096 tokens, n=4, 32/8 heads of 128: 6.1 TB/s of cache rows with the combine
 // (full cross-stream and intra-stream), against 4.4 and 5.2 TB/s with one 256-row workgroup per
 // partial and K loaded straight to registers; streaming loads give 5% over cached ones.
+#include <algorithm>
 #include <mutex>
 
 #include "decode_internal.h"
@@ -68,7 +69,7 @@ __device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
     DecRows r;
     r.kvlen = g.mode == 0 ? ctx + 1 : (ctx + 1) * g.n;
     r.klo = (g.mode == 2 ? max(0, ctx * g.n - g.window + 1) : 0) / kTile * kTile;
-    r.per = dec_split_rows(g.problems, g.D, r.kvlen - r.klo);
+    r.per = dec_split_rows(g.problems, g.D, g.single, r.kvlen - r.klo);
     return r;
 }
 
@@ -80,7 +81,7 @@ __device__ inline void wait_loads_le()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int D, int NW>
+template <int D, int NW, int S>
 __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ kc, const bf16 *__restrict__ vc,
     const int32_t *__restrict__ ctx_tokens, float *__restrict__ part, bf16 *__restrict__ o,
@@ -94,8 +95,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     // the odd row length keeps both its writes, a slot per lane, and its reads, a dim per
     // lane, off one another's banks; then [wave][slot] max and sum)
     constexpr int MERGE = NW * kSlots * (D + 1) * 4 + 2 * NW * kSlots * 4;
-    constexpr int RING = NW * 2 * STAGE;
-    __shared__ __attribute__((aligned(1024))) char smem[MERGE > RING ? MERGE : RING];
+    constexpr int RING = NW * S * STAGE;
+    constexpr int ALL = RING + T::BYTES;  // rings | the query slots
+    static_assert(S == 1 || S == 2, "tiles held per wave");
+    __shared__ __attribute__((aligned(1024))) char smem[MERGE > ALL ? MERGE : ALL];
 
     const DecProblem pr = dec_problem(g, blockIdx.y);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -118,9 +121,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const uint32_t kstride = (uint32_t)(g.mode == 0 ? g.n : 1) * g.Hkv * D * 2;
     const uint32_t kbase = (uint32_t)((g.mode == 0 ? pr.s : 0) * g.Hkv + pr.hk) * D * 2;
 
-    char *const ring = smem + wave * 2 * STAGE;
+    char *const ring = smem + wave * S * STAGE;
+    char *const qtile = smem + RING;
     const auto plan = T::template dma_plan<1>(kbase, kstride, 0, lane);
-    // tile t of the split into stage t / NW % 2; rows past the context load zeros.  Whole
+    // tile t of the split into stage t / NW % S; rows past the context load zeros.  Whole
     // lines read once: streaming loads, unless another head chunk reads the rows too.
     auto issue = [&](int t, char *st) __attribute__((always_inline)) {
         const int row0 = r0 + t * kTile;
@@ -140,17 +144,17 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
         }
     };
 
-    // The 32 query slots (column l32 of the MFMA results is slot l32) come through the ring's
-    // second stage, behind them the first tile.
+    // The 32 query slots (column l32 of the MFMA results is slot l32), shared by the waves, and
+    // behind them the first tile.
     const int nslot = g.nslot;
     {
         const rsrc_t rq = make_rsrc(q, (uint32_t)((size_t)g.B * g.n * g.Hq * D * 2));
 #pragma unroll
-        for (int i = 0; i < T::INSTR; ++i) {
+        for (int i = wave; i < T::INSTR; i += NW) {
             const int x = i * 64 + lane, slot = x / T::CH, c = (x % T::CH) ^ T::swz(slot);
             const int st = g.mode == 0 ? pr.s : slot / g.gchunk;
             const int h = pr.hk * g.G + pr.gc * g.gchunk + (g.mode == 0 ? slot : slot % g.gchunk);
-            dma_lds16(rq, ring + STAGE + i * 1024,
+            dma_lds16(rq, qtile + i * 1024,
                       slot < nslot ? (uint32_t)((((size_t)pr.b * g.n + st) * g.Hq + h) * D * 2) + c * 16 : kOob);
         }
     }
@@ -164,12 +168,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     uint32_t kro[KS], vto[DB][2];
     T::row_offsets(l32, hi, kro);
     T::tr_offsets(lane, vto);
+    lds_barrier();
     bf16x8 qr[KS];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qr[kk] = T::row_at(ring + STAGE, kro[kk], 0);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) pin(qr[kk]);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int kk = 0; kk < KS; ++kk) qr[kk] = T::row_at(qtile, kro[kk], 0);
 
     float m = -INFINITY, lsum = 0.f;
     f32x16 oacc[DB];
@@ -178,9 +180,9 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const float c2 = g.scale_log2;
     const int qp = pos0 + (g.mode == 0 ? 0 : l32 / g.gchunk);  // my query's key coordinate
     for (int i = 0; t < nt; ++i, t += NW) {
-        char *const st = ring + (i & 1) * STAGE;
-        if (t + NW < nt) {
-            issue(t + NW, ring + ((i + 1) & 1) * STAGE);
+        char *const st = ring + i % S * STAGE;
+        if (S == 2 && t + NW < nt) {
+            issue(t + NW, ring + (i + 1) % S * STAGE);
             wait_loads_le<LOADS>();
         } else {
             wait_loads_le<0>();
@@ -236,9 +238,10 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
                 oacc[db] = mfma32(T::tr_at(st + T::BYTES, vto[db], kk), pb[kk], oacc[db]);
-        // this stage is loaded again in the next step: its reads have completed
+        // this stage is loaded again in the next step (or now): its reads have completed
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (S == 1 && t + NW < nt) issue(t + NW, ring);
     }
     mfma_settle();
     lsum = sum_xor32(lsum);
@@ -362,10 +365,13 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     g.nchunk = (int)((rows + kDecChunk - 1) / kDecChunk);
     g.problems = B * Hkv * g.ngc * (mode == 0 ? n : 1);
     g.nslot = g.gchunk * per_head;
-    // the most splits any context up to max_ctx takes; a local layer's rows span at most
-    // the window, the other streams of the token and the rounding down to a tile
-    const int64_t span = mode == 2 && rows > (int64_t)g.window + n + kTile ? (int64_t)g.window + n + kTile : rows;
-    g.nsplit = dec_max_splits(g.problems, D, (int)span);
+    // a local layer's rows span at most the window, the other streams of the token and the
+    // rounding down to a tile
+    const int64_t span = mode == 2 ? (int64_t)window + n + kTile : INT32_MAX;
+    const int64_t cap = mode == 0 ? Lcap : (int64_t)Lcap * n;
+    dec_shape(g.problems, D, (int)std::min(cap, span), g.waves, g.single);
+    // the most splits any context up to max_ctx takes
+    g.nsplit = dec_max_splits(g.problems, D, g.single, (int)std::min(rows, span));
     return g;
 }
 
@@ -412,10 +418,12 @@ hipError_t launch_decode_bf16(const void *q, const void *kc, const void *vc, con
     auto run = [&](auto dk, const char *pname, const char *cname) {
         constexpr int DD = decltype(dk)::value;
         timing_before(pname, s);
-        if (dec_wide(g.problems, DD, g.nsplit))
-            sfa_decode_partial_kernel<DD, 4><<<grid, 4 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+        if (g.waves == 8)
+            sfa_decode_partial_kernel<DD, 8, 1><<<grid, 8 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+        else if (g.waves == 4)
+            sfa_decode_partial_kernel<DD, 4, 2><<<grid, 4 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
         else
-            sfa_decode_partial_kernel<DD, 2><<<grid, 2 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+            sfa_decode_partial_kernel<DD, 2, 2><<<grid, 2 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
         hipError_t e = hipGetLastError();
         timing_after(s);
         if (e != hipSuccess || g.nsplit == 1) return e;
