@@ -197,7 +197,7 @@ constexpr int kSplitGrid = 512;
 // Work items of a dK/dV launch with split sweeps, longest first (a key problem's items
 // are dispatched in this order, so that the workgroups that finish early take the
 // shorter items).  Item i is key tile item[i] >> 2 with code item[i] & 3: 0 the whole
-// sweep, 1 its later half, 2 its earlier half.  A launch has at most kSplitGrid key
+// sweep, 1 its later part, 2 its earlier part.  A launch has at most kSplitGrid key
 // tiles, so 2 * kSplitGrid items.
 struct SplitOrder {
     uint16_t item[2 * kSplitGrid];
@@ -222,9 +222,52 @@ inline int dkdv_splits(const SfaGeom &g)
     return ns;
 }
 
-// The items of a launch with nsplit split key tiles, longest first (ties: lower key
-// tile, later half first).
-inline SplitOrder dkdv_split_order(const SfaGeom &g, int nsplit)
+// Where a launch cuts its long sweeps.  At D=128 (one workgroup per CU) the step can last no
+// less than `cut`, a CU's mean share of all sweeps, and with parts of at most that length,
+// dispatched longest first, it lasts about that: the later part of a split sweep is `cut`
+// long where that is more than half, so that parts of that length fill some CUs whole and the
+// remainders find a partner on the others (causal sweeps of 2, 4 .. T query tiles over T/2 CUs:
+// cut T/2 + 1, and remainders and unsplit sweeps add up to it in pairs).  Halves left such grids
+// at 1.2 mean shares (dK/dV of 2 x 2048 rows, 32/8 heads 192 -> 175 us; 1 x 4096 rows 362 -> 336;
+// 4 streams of 1024 rows 103 -> 92; 2 x 2048 rows, window 1024, 153 -> 145).
+// Where that would split fewer than half of the `most` = dkdv_splits(g) leading tiles (the
+// mean near the longest sweep, or a local layer's sweeps, all about as long) no remainder
+// has a partner, and all of them go in halves, as at D=64 and 32 (20 heads x 2048 rows of 64:
+// 46 us in halves, 48 cut at the mean).
+// `nsplit` <= `most`: the leading tiles that are split.
+struct SplitPlan {
+    int nsplit, cut;
+};
+constexpr int kSplitCus = 256;
+
+__host__ __device__ inline int dkdv_later_part(int len, int cut)
+{
+    const int l = len - len / 2 > cut ? len - len / 2 : cut;
+    return l < len ? l : len;
+}
+
+inline SplitPlan dkdv_split_plan(const SfaGeom &g, int most)
+{
+    const int nkt = (g.len + kDsKeys - 1) / kDsKeys;
+    int64_t sum = 0;
+    int f, e;
+    for (int kt = 0; most > 0 && kt < nkt; ++kt) {
+        dkdv_sweep(g, kt, f, e);
+        sum += e > f ? e - f : 0;
+    }
+    SplitPlan p;
+    p.cut = (int)((sum * g.B * g.Hkv * g.streams + kSplitCus - 1) / kSplitCus);
+    for (p.nsplit = 0; p.nsplit < most; ++p.nsplit) {
+        dkdv_sweep(g, p.nsplit, f, e);
+        if (e - f <= p.cut) break;
+    }
+    if (g.D != 128 || 2 * p.nsplit < most) p = {most, 0};
+    return p;
+}
+
+// The items of a launch with the plan's split key tiles, longest first (ties: lower key
+// tile, later part first).
+inline SplitOrder dkdv_split_order(const SfaGeom &g, const SplitPlan &plan)
 {
     const int nkt = (g.len + kDsKeys - 1) / kDsKeys;
     struct It {
@@ -236,9 +279,10 @@ inline SplitOrder dkdv_split_order(const SfaGeom &g, int nsplit)
         int f, e;
         dkdv_sweep(g, kt, f, e);
         const int len = e > f ? e - f : 0;
-        if (kt < nsplit) {
-            its[n++] = {len - len / 2, kt << 2 | 1};  // later half: [f + len/2, e)
-            its[n++] = {len / 2, kt << 2 | 2};        // earlier half
+        if (kt < plan.nsplit) {
+            const int later = dkdv_later_part(len, plan.cut);
+            its[n++] = {later, kt << 2 | 1};        // later part: [e - later, e)
+            its[n++] = {len - later, kt << 2 | 2};  // earlier part
         } else {
             its[n++] = {len, kt << 2};
         }

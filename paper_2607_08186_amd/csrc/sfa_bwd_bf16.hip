@@ -99,7 +99,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ k, const bf16 *__restrict__ v,
     const bf16 *__restrict__ dO, const float *__restrict__ delta, const float *__restrict__ lse2,
     bf16 *__restrict__ dk, bf16 *__restrict__ dv, bf16 *__restrict__ ds, int64_t ds_tiles, SfaGeom g,
-    QBand bd, int nsplit, float *__restrict__ split, SplitOrder order)
+    QBand bd, int nsplit, int cut, float *__restrict__ split, SplitOrder order)
 {
     constexpr int DB = D / 32, KS = D / 16;
     constexpr int kKeysPerWg = 32 * KW, kDkdvWaves = 2 * KW;
@@ -115,7 +115,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
 
     const int nkt = (g.len + kMaxKeysPerWg - 1) / kMaxKeysPerWg;  // 128-key tiles
     const int nprob = g.B * g.Hkv * g.streams;
-    // work item: a key tile's whole sweep, or with split sweeps (nsplit > 0) one half of
+    // work item: a key tile's whole sweep, or with split sweeps (nsplit > 0) one part of
     // the sweep of one of the first nsplit key tiles, the items taken longest first
     // (the SUB workgroups of a 128-key tile follow one another)
     int prob, rank, ktile, half = -1;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     if (nsplit > 0) {
         const int code = order.item[ktile];
         ktile = code >> 2;
-        half = (code & 3) - 1;  // -1: the whole sweep, 0: its later half, 1: its earlier half
+        half = (code & 3) - 1;  // -1: the whole sweep, 0: its later part, 1: its earlier part
     }
     const int s = prob % g.streams;
     const int hk = (prob / g.streams) % g.Hkv;
@@ -175,8 +175,8 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     if (unseen ? bd.qt_lo != 0 : qt_first >= qt_end) return;  // uniform: nothing to do here
     const bool first_band = unseen || qt_first_all >= bd.qt_lo;
     const bool last_band = unseen || qt_end_all <= bd.qt_hi;
-    if (half >= 0) {  // one half of a split sweep (one pass only): the later tiles, or the earlier
-        const int mid = qt_first + (qt_end - qt_first) / 2;
+    if (half >= 0) {  // one part of a split sweep (one pass only): the later tiles, or the earlier
+        const int mid = qt_end - dkdv_later_part(max(0, qt_end - qt_first), cut);
         if (half == 0)
             qt_first = mid;
         else
@@ -719,18 +719,19 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         bd.part_v = one_pass ? nullptr : reinterpret_cast<float *>(wsb + w.part_v);
         const int64_t band_tiles = tiles(qa, qb);
         // one pass only: the longest sweeps of a small grid are split in halves
-        const int nsplit = one_pass ? w.nsplit : 0;
+        const SplitPlan plan = dkdv_split_plan(g, one_pass ? w.nsplit : 0);
+        const int nsplit = plan.nsplit;
         float *split = reinterpret_cast<float *>(wsb + w.split);
         SplitOrder order;
-        if (nsplit > 0) order = dkdv_split_order(g, nsplit);
+        if (nsplit > 0) order = dkdv_split_order(g, plan);
         timing_before(dkdv_name, s);
         const int items = (nkt + nsplit) * g.B * g.Hkv * g.streams;
         if (items <= kNarrowItems)
             sfa_dkdv_bf16_kernel<D, 2><<<items * 2, 256, 0, s>>>(q, k, v, dO, delta, lse2, dk, dv, ds, band_tiles,
-                                                                 g, bd, nsplit, split, order);
+                                                                 g, bd, nsplit, plan.cut, split, order);
         else
             sfa_dkdv_bf16_kernel<D, 4><<<items, 512, 0, s>>>(q, k, v, dO, delta, lse2, dk, dv, ds, band_tiles,
-                                                             g, bd, nsplit, split, order);
+                                                             g, bd, nsplit, plan.cut, split, order);
         e = hipGetLastError();
         timing_after(s);
         if (e != hipSuccess) return e;

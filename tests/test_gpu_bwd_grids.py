@@ -1,6 +1,6 @@
 """The bf16 backward's block shapes for small and large grids at the edges of their tiles:
 64-key dK/dV workgroups and key-split 128-row dQ blocks (few heads), 128-key and 256-row ones
-(many heads).  Lengths around 64, 128 and 256, an upper half tile without a key, windows
+(many heads); on grids between them the long key sweeps cut at a CU's mean share.  Lengths around 64, 128 and 256, an upper half tile without a key, windows
 that reach one half of a key tile only, final-stream layers, and the smallest workspace
 (query bands), whose dQ must equal the one-pass one bit for bit.  bf16 tolerances of the other
 backward tests."""
@@ -16,7 +16,7 @@ from tests import gpu_helpers as G
 pytestmark = pytest.mark.gpu
 
 INTRA, MIX, LOCAL = 0, 1, 2
-HEADS = {"small": (1, 4, 2), "large": (2, 160, 80)}
+HEADS = {"small": (1, 4, 2), "large": (2, 160, 80), "mid16": (2, 16, 8), "mid60": (5, 12, 12), "mid64": (8, 8, 8)}
 
 
 def _check(heads, D, L, n, mode, window, final):
@@ -76,3 +76,13 @@ def test_large_grids(D, L, n, mode, window):
 @pytest.mark.parametrize("L,n,mode,window", [(2, 5, MIX, 0), (70, 3, MIX, 0), (140, 4, LOCAL, 3), (300, 2, LOCAL, 70)])
 def test_small_final_grids(D, L, n, mode, window):
     _check("small", D, L, n, mode, window, True)
+
+
+# 16, 60 or 64 key problems: the long sweeps are cut at the mean share of 256 CUs (remainders from
+# one query tile up), or in halves where most lie below it or all are about as long
+@pytest.mark.parametrize("D", [32, 128])
+@pytest.mark.parametrize("heads,L,n,mode,window", [
+    ("mid64", 640, 1, MIX, 0), ("mid64", 513, 1, MIX, 0), ("mid60", 577, 1, MIX, 0), ("mid60", 960, 1, LOCAL, 300),
+    ("mid16", 1100, 1, MIX, 0), ("mid16", 560, 2, LOCAL, 500), ("mid16", 640, 2, INTRA, 0)])
+def test_mid_grids(heads, D, L, n, mode, window):
+    _check(heads, D, L, n, mode, window, False)
