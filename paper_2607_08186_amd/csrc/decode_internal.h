@@ -22,29 +22,40 @@ struct DecGeom {
 };
 
 // Split of a problem's cached rows over workgroups.  Up to `single` rows one workgroup takes
-// them all, with no combine pass.  Beyond, the rows are spread so that all problems
-// together make about as many workgroups as the chip holds at once (kDecTarget at D=128:
-// two per CU), in whole tiles of four waves and at least kDecChunk rows each (the workspace
-// has room for that many partials).  16 sequences x 4096 tokens, n=4, 32/8 heads of 128,
-// full cross-stream: 177 us with 512 workgroups, 192 with 1024, 199 with 2048 (more
-// partials, and more prologues that load nothing), 243 with one per 256 rows.
+// them all, with no combine pass.  Beyond, they go in equal parts to as many workgroups as
+// leave all problems together no more of them than the chip holds at once (kDecTarget at D=128:
+// two per CU), in whole tiles and at least kDecChunk rows each (the workspace has room for
+// that many partials).  16 sequences x 4096 tokens, n=4, 32/8 heads of 128, full cross-stream:
+// 177 us with 512 workgroups, 192 with 1024, 199 with 2048 (more partials, and more prologues
+// that load nothing), 243 with one per 256 rows.  Rounded up instead, the workgroups beyond 512
+// run after the others (144 problems of up to 5619 rows: 88.5 us with 4 splits, 69 with 3).
+// Between target / 2 and 2 * target problems long ones go in parts of kDecWhole rows at most, so
+// that contexts of different lengths even out (320 problems of up to 4096 rows, D=128: 120 us
+// whole, 106 in parts; 832 of up to 4796, D=64: 187 and 138; 768 of 2501 rows, D=128, 180 and
+// 173), but not where whole ones about fill the chip (512 of 4096 rows: 175 and 185); with more
+// the chip goes through several rounds of whole ones.  At D=32, where two heads' rows share a
+// line, the parts are of kDecChunk rows (1280 problems of 3001 rows: 188 us whole, 157 in
+// parts of 1024, 106 in parts of 256).
 constexpr int kDecChunk = 256;
 constexpr int kDecTarget = 512;
 __host__ __device__ inline int dec_target(int D) { return kDecTarget * (128 / D); }
+constexpr int kDecWhole = 1024;
+__host__ __device__ inline int dec_splits(int problems, int D, int single, int rows)
+{
+    const int target = dec_target(D);
+    if (rows <= single || (D > 32 && problems >= 2 * target)) return 1;
+    if (D > 32 && problems <= target && problems >= target / 16 * 15) return 1;
+    const int splits = target / problems;
+    const int whole = D > 32 ? kDecWhole : kDecChunk;
+    if (splits <= 1) return (rows + whole - 1) / whole;
+    const int by_rows = (rows + kDecChunk - 1) / kDecChunk;
+    return by_rows < splits ? by_rows : splits;
+}
 __host__ __device__ inline int dec_split_rows(int problems, int D, int single, int rows)
 {
-    if (rows <= single) return single;
-    const int target = dec_target(D);
-    const int64_t per = ((int64_t)rows * problems + target - 1) / target;
-    return per <= kDecChunk ? kDecChunk : (int)((per + 127) / 128 * 128);
-}
-// upper bound of the splits over all sequences of at most `rows` rows
-inline int dec_max_splits(int problems, int D, int single, int rows)
-{
-    if (rows <= single) return 1;
-    const int by_rows = (rows + kDecChunk - 1) / kDecChunk;
-    const int by_target = (dec_target(D) + problems - 1) / problems;
-    return by_rows < by_target ? by_rows : by_target;
+    const int splits = dec_splits(problems, D, single, rows);
+    const int per = (rows + splits - 1) / splits;
+    return splits == 1 ? rows : (per > kDecChunk ? (per + 63) / 64 * 64 : kDecChunk);
 }
 
 // Waves per workgroup and `single`, from the most rows that the cache can hold (and not from
@@ -63,7 +74,7 @@ inline void dec_shape(int problems, int D, int cap_rows, int &waves, int &single
     const int most = problems <= 64 ? 640 : 1024;
     const bool few = problems <= 256 && cap_rows <= most;
     single = few ? most : 384;
-    const int64_t wgs = (int64_t)problems * dec_max_splits(problems, D, single, cap_rows);
+    const int64_t wgs = (int64_t)problems * dec_splits(problems, D, single, cap_rows);
     waves = few ? 8 : wgs <= dec_target(D) / 2 ? 4 : 2;
 }
 

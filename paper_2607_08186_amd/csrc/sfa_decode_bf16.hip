@@ -18,7 +18,7 @@
 //            maximum per query slot, the waves merged through LDS into one (max, sum,
 //            unnormalised O) per query slot in the workspace;
 //   combine: per query row, the splits' partials reduced to o and lse.
-// Where a problem has one split only (short contexts, or enough problems to fill the chip) the
+// Where all problems have one split only (short contexts, or enough problems to fill the chip) the
 // partial kernel writes o and lse itself and the combine is not launched.
 // Measured at 16 x 4096 tokens, n=4, 32/8 heads of 128: 6.1 TB/s of cache rows with the combine
 // (full cross-stream and intra-stream), against 4.4 and 5.2 TB/s with one 256-row workgroup per
@@ -125,11 +125,13 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     char *const qtile = smem + RING;
     const auto plan = T::template dma_plan<1>(kbase, kstride, 0, lane);
     // tile t of the split into stage t / NW % S; rows past the context load zeros.  Whole
-    // lines read once: streaming loads, unless another head chunk reads the rows too.
+    // lines read once: streaming loads, unless another head chunk reads the rows too or, at D=32,
+    // the other half of the line is another head's row (16 x 2597 rows of 3 streams, 64/8 heads
+    // of 32: 50.6 us streaming, 47.3 cached; at D=64 177 streaming and 195 cached).
     auto issue = [&](int t, char *st) __attribute__((always_inline)) {
         const int row0 = r0 + t * kTile;
         const uint32_t off = (uint32_t)row0 * kstride;
-        const bool whole = row0 + kTile <= dr.kvlen, once = g.ngc == 1;
+        const bool whole = row0 + kTile <= dr.kvlen, once = D > 32 && g.ngc == 1;
 #pragma unroll
         for (int i = 0; i < T::INSTR; ++i) {
             uint32_t x = plan.voff[i] + off;
@@ -371,7 +373,7 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     const int64_t cap = mode == 0 ? Lcap : (int64_t)Lcap * n;
     dec_shape(g.problems, D, (int)std::min(cap, span), g.waves, g.single);
     // the most splits any context up to max_ctx takes
-    g.nsplit = dec_max_splits(g.problems, D, g.single, (int)std::min(rows, span));
+    g.nsplit = dec_splits(g.problems, D, g.single, (int)std::min(rows, span));
     return g;
 }
 

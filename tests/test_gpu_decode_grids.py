@@ -24,7 +24,10 @@ CASES = [
     (65, 256, 1, 4, 4, 64, MIX, 0, [255] * 3 + [1] * 62),            # 260 problems, 2 waves
     (3, 900, 4, 8, 2, 128, LOCAL, 500, [899, 130, 0]),  # a window's rows decide, not the cache
     (3, 900, 4, 8, 2, 128, LOCAL, 605, [899, 160, 10]),
-    (1, 1700, 2, 4, 1, 128, MIX, 0, [1699]),            # 4 waves, 13 splits
+    (1, 1700, 2, 4, 1, 128, MIX, 0, [1699]),            # 4 waves, 14 splits
+    (38, 1100, 1, 16, 16, 64, MIX, 0, [1099, 1023, 1024, 700] + [3] * 34),  # 608 problems: parts of 1024
+    (31, 600, 1, 16, 16, 128, MIX, 0, [599, 384] + [5] * 29),               # 496: whole
+    (72, 520, 1, 16, 16, 32, MIX, 0, [519, 385, 384] + [9] * 69),           # 1152: parts of 256
 ]
 
 
