@@ -332,7 +332,8 @@ hd_status_t hd_sfa_bwd_final(const void *q, const void *k, const void *v, const 
  * q               device bf16 [B][n][Hq][D], the new token's n query rows per sequence.
  * k_cache,v_cache device bf16 [B][n*Lcap][Hkv][D], expanded rows p = t*n + s (grouped
  *                 heads as in hd_sfa_fwd).
- * ctx_tokens      device int32 [B], each in [0, max_ctx_tokens].
+ * ctx_tokens      device int32 [B], each in [0, max_ctx_tokens]; one outside counts as the
+ *                 nearest value inside.
  * max_ctx_tokens  host bound on ctx_tokens (sizes the launch and the workspace), < Lcap.
  * o               device bf16 [B][n][Hq][D];  lse  device float [B][Hq][n] (natural log).
  * window          the local window (HD_SFA_LOCAL, >= 1); ignored by the other modes.

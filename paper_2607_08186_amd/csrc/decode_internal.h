@@ -10,6 +10,7 @@ struct DecGeom {
     int B, Lcap, n, Hq, Hkv, D, G;
     int mode;          // 0 intra, 1 full cross-stream, 2 local cross-stream
     int window;        // local layers: positions p - window < p' <= p; else a huge value
+    int max_ctx;       // bound on the contexts
     float scale_log2;  // scale * log2(e)
     int gchunk;        // query heads per problem (their query slots fit 32 MFMA columns)
     int ngc;           // head chunks per key/value head, G / gchunk
@@ -76,6 +77,25 @@ inline void dec_shape(int problems, int D, int cap_rows, int &waves, int &single
     single = few ? most : 384;
     const int64_t wgs = (int64_t)problems * dec_splits(problems, D, single, cap_rows);
     waves = few ? 8 : wgs <= dec_target(D) / 2 ? 4 : 2;
+}
+
+// Cached rows of a problem that some query row of it sees: [klo, kvlen), the first one
+// rounded down to a tile of kDecTile; they are split over workgroups, `per` rows each.  A
+// context outside [0, max_ctx], for which neither grid nor workspace is made, counts as the
+// nearest one inside.
+constexpr int kDecTile = 32;  // cached rows per wave and step
+struct DecRows {
+    int ctx, klo, kvlen, per;
+};
+__host__ __device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
+{
+    DecRows r;
+    r.ctx = ctx < 0 ? 0 : ctx > g.max_ctx ? g.max_ctx : ctx;
+    r.kvlen = g.mode == 0 ? r.ctx + 1 : (r.ctx + 1) * g.n;
+    const int lo = r.ctx * g.n - g.window + 1;  // first position in the window of stream 0
+    r.klo = (g.mode == 2 && lo > 0 ? lo : 0) / kDecTile * kDecTile;
+    r.per = dec_split_rows(g.problems, g.D, g.single, r.kvlen - r.klo);
+    return r;
 }
 
 DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, int window,

@@ -33,7 +33,7 @@ namespace hd {
 
 namespace {
 
-constexpr int kTile = 32;                     // cached rows per wave and step
+constexpr int kTile = kDecTile;               // cached rows per wave and step
 constexpr int kSlots = 32;                    // query slots per problem (MFMA columns)
 
 // problem index -> (b, kv head, head chunk, stream) and the problem's query slots:
@@ -55,21 +55,6 @@ __device__ inline DecProblem dec_problem(const DecGeom &g, int p)
     p /= g.ngc;
     r.hk = p % g.Hkv;
     r.b = p / g.Hkv;
-    return r;
-}
-
-// cached rows of a problem that some query row of it sees: [klo, kvlen), the first one
-// rounded down to a tile; they are split over nsplit workgroups, `per` rows each
-struct DecRows {
-    int klo, kvlen, per;
-};
-
-__device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
-{
-    DecRows r;
-    r.kvlen = g.mode == 0 ? ctx + 1 : (ctx + 1) * g.n;
-    r.klo = (g.mode == 2 ? max(0, ctx * g.n - g.window + 1) : 0) / kTile * kTile;
-    r.per = dec_split_rows(g.problems, g.D, g.single, r.kvlen - r.klo);
     return r;
 }
 
@@ -105,9 +90,8 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
 
-    const int ctx = ctx_tokens[pr.b];
-    const DecRows dr = dec_rows(g, ctx);
-    const int pos0 = ctx * g.n;  // expanded position of the new token's stream 0
+    const DecRows dr = dec_rows(g, ctx_tokens[pr.b]);
+    const int pos0 = dr.ctx * g.n;  // expanded position of the new token's stream 0
     // this workgroup's rows: cross-stream rows are expanded positions, intra-stream problem
     // row j is cache row j*n + s
     const int r0 = dr.klo + (int)blockIdx.x * dr.per;
@@ -352,6 +336,7 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     DecGeom g;
     g.B = B; g.Lcap = Lcap; g.n = n; g.Hq = Hq; g.Hkv = Hkv; g.D = D; g.G = Hq / Hkv;
     g.mode = mode;
+    g.max_ctx = max_ctx;
     g.window = mode == 2 ? window : kNoWindow;
     g.scale_log2 = scale * 1.4426950408889634f;
     // query heads per problem: the largest divisor of G whose slots fit the 32 columns

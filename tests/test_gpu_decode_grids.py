@@ -46,3 +46,16 @@ def test_decode_grids(case):
     a, b = _run(ins, low, mode, w), _run(ins, low, mode, w, max_ctx=Lcap - 1)
     np.testing.assert_array_equal(a[0], b[0])
     np.testing.assert_array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("mode,w", [(MIX, 0), (INTRA, 0), (LOCAL, 300)])
+def test_decode_context_outside_the_bound(mode, w):
+    """A context below 0 or past the bound counts as the nearest one inside: grid and workspace
+    are made for the bound, and nothing beyond them is read or written."""
+    B, Lcap, n, Hq, Hkv, D = 3, 900, 4, 8, 2, 64
+    ins = _inputs(synth.seed_for("decode-outside", mode), B, Lcap, n, Hq, Hkv, D)
+    a = _run(ins, [-3, 899, 100], mode, w, max_ctx=500)
+    b = _run(ins, [0, 500, 100], mode, w, max_ctx=500)
+    np.testing.assert_array_equal(a[0], b[0])
+    np.testing.assert_array_equal(a[1], b[1])
+    assert np.all(np.isfinite(a[0]))
