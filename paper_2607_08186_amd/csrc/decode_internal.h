@@ -19,6 +19,7 @@ struct DecGeom {
     int problems;      // B * Hkv * ngc (* n for intra-stream layers)
     int nslot;         // query slots per problem: gchunk (intra-stream) or n * gchunk
     int waves;         // per workgroup of the partial kernel: 2, 4 or 8
+    int heads;         // neighbouring key/value heads that one XCD takes together
     int single;        // cached rows up to which one workgroup takes a whole problem
 };
 
@@ -59,6 +60,17 @@ __host__ __device__ inline int dec_split_rows(int problems, int D, int single, i
     return splits == 1 ? rows : (per > kDecChunk ? (per + 63) / 64 * 64 : kDecChunk);
 }
 
+// Neighbouring key/value heads that one XCD takes together.  At D=32 two heads' rows share a line,
+// and on large grids their lying side by side counts as well, so up to eight (D=32, 16 sequences x
+// 4096 rows x 4 streams: 50 us, 87 a head at a time; D=64, 1280 problems of 3000 rows: 164 and 182);
+// below, single heads spread a step better (D=64, 128 problems of 16384 rows: 98 and 106).
+inline int dec_heads(int problems, int D, int Hkv)
+{
+    int h = D == 32 || problems > 256 ? 8 : 1;
+    while (Hkv % h) h /= 2;
+    return h;
+}
+
 // Waves per workgroup and `single`, from the most rows that the cache can hold (and not from
 // the bound on this call's contexts, so that a sequence's result does not depend on it):
 //   8 waves, one tile in flight each, where at most one problem per CU has at most 1024
@@ -96,6 +108,46 @@ __host__ __device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
     r.klo = (g.mode == 2 && lo > 0 ? lo : 0) / kDecTile * kDecTile;
     r.per = dec_split_rows(g.problems, g.D, g.single, r.kvlen - r.klo);
     return r;
+}
+
+// A problem and its query slots: cross-stream layers: slot = s * gchunk + head-in-chunk (all
+// streams of the token); intra-stream layers: one problem per stream, slot = head-in-chunk.
+struct DecProblem {
+    int b, hk, gc, s;
+};
+
+__host__ __device__ inline int dec_index(const DecGeom &g, const DecProblem &r)
+{
+    return ((r.b * g.Hkv + r.hk) * g.ngc + r.gc) * (g.mode == 0 ? g.n : 1) + r.s;
+}
+
+// Workgroup id -> problem and split.  Ids go round-robin over the 8 XCDs; `heads` neighbouring
+// key/value heads, whose rows share lines or lie side by side, follow each other on one XCD, and
+// such units are dealt out over the XCDs split by split, so that splits past the end of a short
+// context leave no XCD out.  False: no work.
+__host__ __device__ inline bool dec_place(const DecGeom &g, int id, DecProblem &r, int &split)
+{
+    const int j = id >> 3, unit = (j / g.heads << 3) + (id & 7), units = g.problems / g.heads;
+    split = unit / units;
+    if (split >= g.nsplit) return false;
+    int p = unit % units;
+    r.s = 0;
+    if (g.mode == 0) {
+        r.s = p % g.n;
+        p /= g.n;
+    }
+    r.gc = p % g.ngc;
+    p /= g.ngc;
+    const int sets = g.Hkv / g.heads;
+    r.hk = p % sets * g.heads + j % g.heads;
+    r.b = p / sets;
+    return true;
+}
+
+// workgroup ids that dec_place maps
+inline int64_t dec_grid(const DecGeom &g)
+{
+    return ((int64_t)g.problems / g.heads * g.nsplit + 7) / 8 * 8 * g.heads;
 }
 
 DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, int window,

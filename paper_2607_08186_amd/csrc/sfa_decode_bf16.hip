@@ -36,28 +36,6 @@ namespace {
 constexpr int kTile = kDecTile;               // cached rows per wave and step
 constexpr int kSlots = 32;                    // query slots per problem (MFMA columns)
 
-// problem index -> (b, kv head, head chunk, stream) and the problem's query slots:
-// cross-stream layers: slot = s * gchunk + head-in-chunk (all streams of the token);
-// intra-stream layers: one problem per stream, slot = head-in-chunk.
-struct DecProblem {
-    int b, hk, gc, s;
-};
-
-__device__ inline DecProblem dec_problem(const DecGeom &g, int p)
-{
-    DecProblem r;
-    r.s = 0;
-    if (g.mode == 0) {
-        r.s = p % g.n;
-        p /= g.n;
-    }
-    r.gc = p % g.ngc;
-    p /= g.ngc;
-    r.hk = p % g.Hkv;
-    r.b = p / g.Hkv;
-    return r;
-}
-
 template <int N>
 __device__ inline void wait_loads_le()
 {
@@ -85,7 +63,9 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     static_assert(S == 1 || S == 2, "tiles held per wave");
     __shared__ __attribute__((aligned(1024))) char smem[MERGE > ALL ? MERGE : ALL];
 
-    const DecProblem pr = dec_problem(g, blockIdx.y);
+    DecProblem pr;
+    int split;
+    if (!dec_place(g, blockIdx.x, pr, split)) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
@@ -94,7 +74,7 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const int pos0 = dr.ctx * g.n;  // expanded position of the new token's stream 0
     // this workgroup's rows: cross-stream rows are expanded positions, intra-stream problem
     // row j is cache row j*n + s
-    const int r0 = dr.klo + (int)blockIdx.x * dr.per;
+    const int r0 = dr.klo + split * dr.per;
     if (r0 >= dr.kvlen) return;  // the combine reads the splits that have rows
     const int r1 = min(dr.kvlen, r0 + dr.per);
     const int nt = (r1 - r0 + kTile - 1) / kTile;
@@ -251,7 +231,7 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     __syncthreads();
     // partials [problem][split][slot][D + 2]: O, then max and sum, for the problem's
     // nslot slots only; with one split per problem the results themselves
-    float *dst = part + ((size_t)blockIdx.y * g.nsplit + blockIdx.x) * nslot * (D + 2);
+    float *dst = part + ((size_t)dec_index(g, pr) * g.nsplit + split) * nslot * (D + 2);
     for (int e = tid; e < nslot * D; e += NW * 64) {
         const int sl_i = e / D, d = e % D;
         float mt = -INFINITY;
@@ -291,15 +271,9 @@ __global__ __launch_bounds__(D) void sfa_decode_combine_kernel(const float *__re
     const int hq = blockIdx.x % g.Hq;
     const int s = (blockIdx.x / g.Hq) % g.n;
     const int b = blockIdx.x / (g.Hq * g.n);
-    const int hk = hq / g.G, gc = (hq % g.G) / g.gchunk, gl = (hq % g.G) % g.gchunk;
-    int prob = (b * g.Hkv + hk) * g.ngc + gc;
-    int slot;
-    if (g.mode == 0) {
-        prob = prob * g.n + s;
-        slot = gl;
-    } else {
-        slot = s * g.gchunk + gl;
-    }
+    const int gl = (hq % g.G) % g.gchunk;
+    const int prob = dec_index(g, DecProblem{b, hq / g.G, (hq % g.G) / g.gchunk, g.mode == 0 ? s : 0});
+    const int slot = g.mode == 0 ? gl : s * g.gchunk + gl;
     // the splits the partial kernel wrote: those with rows
     const DecRows dr = dec_rows(g, ctx_tokens[b]);
     const int nc = (dr.kvlen - dr.klo + dr.per - 1) / dr.per;
@@ -352,6 +326,7 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     g.nchunk = (int)((rows + kDecChunk - 1) / kDecChunk);
     g.problems = B * Hkv * g.ngc * (mode == 0 ? n : 1);
     g.nslot = g.gchunk * per_head;
+    g.heads = dec_heads(g.problems, D, Hkv);
     // a local layer's rows span at most the window, the other streams of the token and the
     // rounding down to a tile
     const int64_t span = mode == 2 ? (int64_t)window + n + kTile : INT32_MAX;
@@ -400,7 +375,7 @@ hipError_t launch_decode_bf16(const void *q, const void *kc, const void *vc, con
                *vv = static_cast<const bf16 *>(vc);
     float *part = static_cast<float *>(ws);
     bf16 *oo = static_cast<bf16 *>(o);
-    const dim3 grid(g.nsplit, g.problems);
+    const unsigned grid = (unsigned)dec_grid(g);
     const int rows = g.B * g.n * g.Hq;
     auto run = [&](auto dk, const char *pname, const char *cname) {
         constexpr int DD = decltype(dk)::value;

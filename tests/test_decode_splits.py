@@ -6,7 +6,10 @@ each, that
   * the splits with rows cover a problem's visible rows once and are no more than the launch
     has and the workspace has room for;
   * a context outside [0, bound] counts as the nearest one inside, so that no index leaves the
-    grid, the workspace or the cache.
+    grid, the workspace or the cache;
+  * every (problem, split) has exactly one workgroup, neighbouring heads that share cache lines
+    stay on one XCD, and the first splits alone - all that short contexts under a loose bound
+    leave - spread over the XCDs to within one unit of heads.
 """
 import os
 import shutil
@@ -23,6 +26,7 @@ PROGRAM = r"""
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "decode_internal.h"
 
@@ -71,6 +75,44 @@ int main()
                                     ++cases;
                                 }
                             }
+                        }
+    for (const auto &h : heads)
+        for (int D : {32, 64, 128})
+            for (int n : {1, 4})
+                for (int B : {1, 3, 8, 40})
+                    for (int mode : {0, 1})
+                        for (int bound : {100, 2000, 20000}) {
+                            const DecGeom g = make_dec_geom(B, bound + 1, n, h[0], h[1], D, mode, 0, 1.f, bound);
+                            const int ctx = bound;
+                            std::vector<int> seen((size_t)g.problems * g.nsplit);
+                            std::vector<int> xcd((size_t)g.problems), load(8);
+                            const int64_t grid = dec_grid(g);
+                            CHECK(grid < (1LL << 31));
+                            for (int64_t id = 0; id < grid; ++id) {
+                                DecProblem p;
+                                int split;
+                                if (!dec_place(g, (int)id, p, split)) continue;
+                                const int ix = dec_index(g, p);
+                                CHECK(p.b >= 0 && p.b < B && p.hk >= 0 && p.hk < g.Hkv && p.gc >= 0 && p.gc < g.ngc);
+                                CHECK(p.s >= 0 && p.s < (mode == 0 ? n : 1) && split >= 0 && split < g.nsplit);
+                                CHECK(ix >= 0 && ix < g.problems);
+                                ++seen[(size_t)ix * g.nsplit + split];
+                                if (split == 0) {
+                                    xcd[ix] = (int)(id & 7);
+                                    ++load[id & 7];
+                                }
+                            }
+                            for (int s : seen) CHECK(s == 1);
+                            CHECK(*std::max_element(load.begin(), load.end()) -
+                                      *std::min_element(load.begin(), load.end()) <= g.heads);
+                            if (D == 32)  // two neighbouring heads' rows fill one 128-byte line
+                                for (int b = 0; b < B; ++b)
+                                    for (int hk = 0; hk + 1 < g.Hkv; hk += 2) {
+                                        if (g.Hkv % 2) continue;
+                                        CHECK(xcd[dec_index(g, DecProblem{b, hk, 0, 0})] ==
+                                              xcd[dec_index(g, DecProblem{b, hk + 1, 0, 0})]);
+                                    }
+                            ++cases;
                         }
     std::printf("%ld cases\n", cases);
     return 0;
