@@ -15,80 +15,51 @@ struct DecGeom {
     int gchunk;        // query heads per problem (their query slots fit 32 MFMA columns)
     int ngc;           // head chunks per key/value head, G / gchunk
     int nchunk;        // 256-row chunks of the cache per problem (for the longest context)
-    int nsplit;        // workgroups per problem (for the longest context), at most nchunk
     int problems;      // B * Hkv * ngc (* n for intra-stream layers)
     int nslot;         // query slots per problem: gchunk (intra-stream) or n * gchunk
-    int waves;         // per workgroup of the partial kernel: 2, 4 or 8
+    int waves;         // per workgroup of the partial kernel: 8 or 4
     int heads;         // neighbouring key/value heads that one XCD takes together
-    int single;        // cached rows up to which one workgroup takes a whole problem
+    int single, fill, whole, part;  // see dec_splits
+    int nsplit;        // workgroups per problem (for the longest context), at most nchunk
 };
 
-// Split of a problem's cached rows over workgroups.  Up to `single` rows one workgroup takes
-// them all, with no combine pass.  Beyond, they go in equal parts to as many workgroups as
-// leave all problems together no more of them than the chip holds at once (kDecTarget at D=128:
-// two per CU), in whole tiles and at least kDecChunk rows each (the workspace has room for
-// that many partials).  16 sequences x 4096 tokens, n=4, 32/8 heads of 128, full cross-stream:
-// 177 us with 512 workgroups, 192 with 1024, 199 with 2048 (more partials, and more prologues
-// that load nothing), 243 with one per 256 rows.  Rounded up instead, the workgroups beyond 512
-// run after the others (144 problems of up to 5619 rows: 88.5 us with 4 splits, 69 with 3).
-// Between target / 2 and 2 * target problems long ones go in parts of kDecWhole rows at most, so
-// that contexts of different lengths even out (320 problems of up to 4096 rows, D=128: 120 us
-// whole, 106 in parts; 832 of up to 4796, D=64: 187 and 138; 768 of 2501 rows, D=128, 180 and
-// 173), but not where whole ones about fill the chip (512 of 4096 rows: 175 and 185); with more
-// the chip goes through several rounds of whole ones.  At D=32, where two heads' rows share a
-// line, the parts are of kDecChunk rows (1280 problems of 3001 rows: 188 us whole, 157 in
-// parts of 1024, 106 in parts of 256).
+// Split of a problem's cached rows over workgroups.  It follows from the number of problems,
+// the head dim and the sequence's own rows, and neither from the cache's capacity nor from the
+// bound on the contexts: these change no bit of a result, and no short context pays for a large
+// cache (D=128, launch to launch, 32 to 256 problems of 100 to 1000 rows in a cache of 4096: 10.7 to 22
+// us, as in a tight one; shaped by the capacity they took 14.7 to 28.6).
+//   Workgroups: eight waves, one workgroup per CU, up to 256 problems at D=128; half of that each
+//     beyond (256 CUs; 264 problems of 700 rows 23.6 -> 22.7 us) and, where a tile is half the
+//     bytes or less, from 65 problems on (D=64: 96 of 2000 rows 18.9 -> 15.5).
+//   Up to `single` rows one workgroup takes a problem, and where that holds for all of them the
+//     combine is not launched (64 problems x 499 rows 11.4 us, 14.8 in parts; 256 x 1000 rows 22 and
+//     32; but 32 x 777 rows are faster in parts, 13.8 and 15.6).
+//   Beyond, at least `fill` parts, with which all problems together fill the chip once, of at
+//     least kDecChunk rows each (the workspace has room for that many partials).  More of them
+//     mean more prologues and partials (16 x 4096 tokens, n=4, 32/8 heads of 128, full
+//     cross-stream: 169 us in 2 parts, 174 in 4).
+//   Above 256 problems parts of at most `part` rows even out contexts of different lengths and
+//     the last round of workgroups (264 problems of 6000 rows at D=128: 149 us, 182 whole; 560 of
+//     4500 at D=64: 106 and 142).  So do they where `fill` is one part for 129 to 170 problems, a
+//     third of the CUs or more idle, in long contexts (`whole`; 160 of up to 6000 rows, D=128: 70
+//     us, 80 whole; but 184 of 6000 rows 109 and 93).  Not at D=128 where whole ones fill seven
+//     eighths or more of the 512 places (448 of 4500 rows: 175 us in parts, 166 whole; 512 of 4096: 172
+//     and 165; 384 of 4500: 149 and 154).
+constexpr int kDecSlots = 8;  // waves that a CU holds at D=128, each with a K and a V tile in LDS
 constexpr int kDecChunk = 256;
-constexpr int kDecTarget = 512;
-__host__ __device__ inline int dec_target(int D) { return kDecTarget * (128 / D); }
-constexpr int kDecWhole = 1024;
-__host__ __device__ inline int dec_splits(int problems, int D, int single, int rows)
+__host__ __device__ inline int dec_splits(const DecGeom &g, int rows)
 {
-    const int target = dec_target(D);
-    if (rows <= single || (D > 32 && problems >= 2 * target)) return 1;
-    if (D > 32 && problems <= target && problems >= target / 16 * 15) return 1;
-    const int splits = target / problems;
-    const int whole = D > 32 ? kDecWhole : kDecChunk;
-    if (splits <= 1) return (rows + whole - 1) / whole;
+    if (rows <= g.single) return 1;
     const int by_rows = (rows + kDecChunk - 1) / kDecChunk;
-    return by_rows < splits ? by_rows : splits;
+    const int parts = rows <= g.whole ? 1 : (rows + g.part - 1) / g.part;
+    const int want = parts > g.fill ? parts : g.fill;
+    return want < by_rows ? want : by_rows;
 }
-__host__ __device__ inline int dec_split_rows(int problems, int D, int single, int rows)
+__host__ __device__ inline int dec_split_rows(const DecGeom &g, int rows)
 {
-    const int splits = dec_splits(problems, D, single, rows);
+    const int splits = dec_splits(g, rows);
     const int per = (rows + splits - 1) / splits;
     return splits == 1 ? rows : (per > kDecChunk ? (per + 63) / 64 * 64 : kDecChunk);
-}
-
-// Neighbouring key/value heads that one XCD takes together.  At D=32 two heads' rows share a line,
-// and on large grids their lying side by side counts as well, so up to eight (D=32, 16 sequences x
-// 4096 rows x 4 streams: 50 us, 87 a head at a time; D=64, 1280 problems of 3000 rows: 164 and 182);
-// below, single heads spread a step better (D=64, 128 problems of 16384 rows: 98 and 106).
-inline int dec_heads(int problems, int D, int Hkv)
-{
-    int h = D == 32 || problems > 256 ? 8 : 1;
-    while (Hkv % h) h /= 2;
-    return h;
-}
-
-// Waves per workgroup and `single`, from the most rows that the cache can hold (and not from
-// the bound on this call's contexts, so that a sequence's result does not depend on it):
-//   8 waves, one tile in flight each, where at most one problem per CU has at most 1024
-//     rows: the whole problem in one launch (D=128, launch to launch: 256 problems x 501 rows
-//     22.1 us in 2 splits, 15.5 in one; x 1001 rows 32 and 26.5; 128 x 801 rows 18.6 and
-//     15.9).  With 64 problems or fewer the split's larger grid wins earlier (64 x 516 rows
-//     15.8 and 14.7, 32 x 764 rows 15.1 and 15.6);
-//   4 waves, two tiles in flight each, where that leaves at most one workgroup per CU: few
-//     rows in all, whose latency counts (8 problems x 3112 rows: 16.1 us against 19.3);
-//   2 waves else: two workgroups per CU overlap each other's prologue and merge (32 problems
-//     x 4096 rows 20.0 us against 22.5, 32 x 8004 rows 35 against 48).
-inline void dec_shape(int problems, int D, int cap_rows, int &waves, int &single)
-{
-    const int most = problems <= 64 ? 640 : 1024;
-    const bool few = problems <= 256 && cap_rows <= most;
-    single = few ? most : 384;
-    const int64_t wgs = (int64_t)problems * dec_splits(problems, D, single, cap_rows);
-    waves = few ? 8 : wgs <= dec_target(D) / 2 ? 4 : 2;
 }
 
 // Cached rows of a problem that some query row of it sees: [klo, kvlen), the first one
@@ -106,8 +77,28 @@ __host__ __device__ inline DecRows dec_rows(const DecGeom &g, int ctx)
     r.kvlen = g.mode == 0 ? r.ctx + 1 : (r.ctx + 1) * g.n;
     const int lo = r.ctx * g.n - g.window + 1;  // first position in the window of stream 0
     r.klo = (g.mode == 2 && lo > 0 ? lo : 0) / kDecTile * kDecTile;
-    r.per = dec_split_rows(g.problems, g.D, g.single, r.kvlen - r.klo);
+    r.per = dec_split_rows(g, r.kvlen - r.klo);
     return r;
+}
+
+// Shape of the launch (see dec_splits), for problems of at most `rows` visible rows.
+//   heads: at D=32 two heads' rows share a line, and on large grids their lying side by side
+//     counts as well, so one XCD takes up to eight neighbouring heads together (D=32, 16 sequences
+//     x 4096 rows x 4 streams: 50 us, 87 a head at a time; D=64, 1280 problems of 3000 rows: 164 and
+//     182); below, single heads spread a step better (D=64, 128 problems of 16384 rows: 98 and 106).
+inline void dec_launch(DecGeom &g, int rows)
+{
+    const int P = g.problems;
+    g.waves = P <= (g.D == 128 ? 256 : 64) ? 8 : 4;
+    g.single = P <= 64 ? 640 : P <= 256 ? 1024 : 384;
+    g.fill = kCus * (kDecSlots / g.waves) * (128 / g.D) / P;
+    g.part = g.D == 128 ? 2048 : 1024;
+    g.whole = P > 256 ? g.part : 1 << 30;
+    if (g.D == 128 && P > 128 && P <= 170) g.whole = 4096;
+    if (g.D == 128 && P >= 448 && P <= 512) g.whole = 1 << 30;
+    g.heads = g.D == 32 || P > 256 ? 8 : 1;
+    while (g.Hkv % g.heads) g.heads /= 2;
+    g.nsplit = dec_splits(g, rows);  // grows with the rows
 }
 
 // A problem and its query slots: cross-stream layers: slot = s * gchunk + head-in-chunk (all

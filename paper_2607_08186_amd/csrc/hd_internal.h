@@ -34,6 +34,8 @@ struct SfaGeom {
 
 constexpr int kNoWindow = 1 << 30;
 
+constexpr int kCus = 256;  // compute units of the MI355X, which grid rules are written for
+
 // Problem geometry of one call.  Local cross-stream layers decompose like the full
 // cross-stream layer (one problem per (b, hq) over all N rows) with a window.
 inline SfaGeom make_geom(int B, int L, int n, int Hq, int Hkv, int D, int mode, float scale,
@@ -238,7 +240,6 @@ inline int dkdv_splits(const SfaGeom &g)
 struct SplitPlan {
     int nsplit, cut;
 };
-constexpr int kSplitCus = 256;
 
 __host__ __device__ inline int dkdv_later_part(int len, int cut)
 {
@@ -256,7 +257,7 @@ inline SplitPlan dkdv_split_plan(const SfaGeom &g, int most)
         sum += e > f ? e - f : 0;
     }
     SplitPlan p;
-    p.cut = (int)((sum * g.B * g.Hkv * g.streams + kSplitCus - 1) / kSplitCus);
+    p.cut = (int)((sum * g.B * g.Hkv * g.streams + kCus - 1) / kCus);
     for (p.nsplit = 0; p.nsplit < most; ++p.nsplit) {
         dkdv_sweep(g, p.nsplit, f, e);
         if (e - f <= p.cut) break;

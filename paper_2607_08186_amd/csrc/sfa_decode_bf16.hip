@@ -9,22 +9,22 @@
 //
 // HBM-bound: every cached key/value row is read once for all the query rows that use it
 // (the heads of its group, and for cross-stream layers all n streams: up to 32 query
-// slots per problem).  Split over the cache:
+// slots per problem).  Split over the cache (dec_splits):
 //   partial: a workgroup takes one split of the cached rows of one problem (b, kv-head[,
-//            head chunk][, stream]); its waves take 32-row tiles in turn, each through a ring of
-//            its own in LDS that holds two tiles of K and V (direct-to-LDS streaming loads
-//            of whole lines, the next tile in flight while one is used, no barrier in the
-//            loop), S^T = K Q^T and O^T += V^T P^T on the matrix cores with a running
-//            maximum per query slot, the waves merged through LDS into one (max, sum,
-//            unnormalised O) per query slot in the workspace;
+//            head chunk][, stream]); its waves take 32-row tiles in turn, K and V each through a
+//            place of its own in LDS that the next tile's rows are loaded into as soon as this one's
+//            are used (direct-to-LDS streaming loads of whole lines, no barrier in the loop),
+//            S^T = K Q^T and O^T += V^T P^T on the matrix cores with a running maximum per
+//            query slot, the waves merged through LDS into one (max, sum, unnormalised O)
+//            per query slot in the workspace;
 //   combine: per query row, the splits' partials reduced to o and lse.
 // Where all problems have one split only (short contexts, or enough problems to fill the chip) the
 // partial kernel writes o and lse itself and the combine is not launched.
-// Measured at 16 x 4096 tokens, n=4, 32/8 heads of 128: 6.1 TB/s of cache rows with the combine
-// (full cross-stream and intra-stream), against 4.4 and 5.2 TB/s with one 256-row workgroup per
-// partial and K loaded straight to registers; streaming loads give 5% over cached ones.
+// Measured at 16 x 4096 tokens, n=4, 32/8 heads of 128: 6.3 TB/s of cache rows with the combine
+// (full cross-stream and intra-stream); streaming loads give 5% over cached ones.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "decode_internal.h"
 #include "sfa_lds.h"
@@ -36,6 +36,26 @@ namespace {
 constexpr int kTile = kDecTile;               // cached rows per wave and step
 constexpr int kSlots = 32;                    // query slots per problem (MFMA columns)
 
+// What a tile's rows see: rows below < j <= limit are visible to this lane's query (they exist
+// and, for cross-stream layers, lie at or before it and within the window).
+struct Mask {
+    int kvlen, pos0, n, window, limit, below;
+    bool cross;
+    __device__ inline Mask(const DecGeom &g, const DecRows &r, int slot)
+        : kvlen(r.kvlen), pos0(r.ctx * g.n), n(g.n), window(g.window), cross(g.mode != 0)
+    {
+        const int qp = pos0 + slot / g.gchunk;  // my query's key coordinate (cross-stream layers)
+        limit = cross ? min(qp, kvlen - 1) : kvlen - 1;
+        below = cross ? max(-1, qp - window) : -1;
+    }
+    // the tile at row kb holds a pair that is not visible (uniform over the wave)
+    __device__ inline bool some(int kb) const
+    {
+        const int last = kb + kTile - 1;
+        return last >= kvlen || (cross && (last > pos0 || pos0 + n - 1 - kb >= window));
+    }
+};
+
 template <int N>
 __device__ inline void wait_loads_le()
 {
@@ -44,7 +64,8 @@ __device__ inline void wait_loads_le()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int D, int NW, int S>
+// NW waves; ONCE: each line of the cache serves one problem only (streaming loads).
+template <int D, int NW, bool ONCE>
 __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const bf16 *__restrict__ q, const bf16 *__restrict__ kc, const bf16 *__restrict__ vc,
     const int32_t *__restrict__ ctx_tokens, float *__restrict__ part, bf16 *__restrict__ o,
@@ -52,15 +73,13 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
 {
     constexpr int KS = D / 16, DB = D / 32;
     using T = Tile<D, kTile>;
-    constexpr int STAGE = 2 * T::BYTES;  // K rows | V rows
-    constexpr int LOADS = 2 * T::INSTR;  // direct-to-LDS instructions per stage
-    // the rings, reused at the end as the scratch of the merge ([wave][slot][D + 1] of O:
-    // the odd row length keeps both its writes, a slot per lane, and its reads, a dim per
-    // lane, off one another's banks; then [wave][slot] max and sum)
+    constexpr int LOADS = T::INSTR;  // direct-to-LDS instructions per K or V tile
+    // LDS: K and V tile of each wave, reused at the end as the scratch of the merge
+    // ([wave][slot][D + 1] of O: the odd row length keeps both its writes, a slot per lane, and
+    // its reads, a dim per lane, off one another's banks; then [wave][slot] max and sum)
     constexpr int MERGE = NW * kSlots * (D + 1) * 4 + 2 * NW * kSlots * 4;
-    constexpr int RING = NW * S * STAGE;
-    constexpr int ALL = RING + T::BYTES;  // rings | the query slots
-    static_assert(S == 1 || S == 2, "tiles held per wave");
+    constexpr int TILES = NW * 2 * T::BYTES;
+    constexpr int ALL = TILES + T::BYTES;  // tiles | the query slots
     __shared__ __attribute__((aligned(1024))) char smem[MERGE > ALL ? MERGE : ALL];
 
     DecProblem pr;
@@ -71,52 +90,45 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
     const int l32 = lane & 31, hi = lane >> 5;
 
     const DecRows dr = dec_rows(g, ctx_tokens[pr.b]);
-    const int pos0 = dr.ctx * g.n;  // expanded position of the new token's stream 0
     // this workgroup's rows: cross-stream rows are expanded positions, intra-stream problem
     // row j is cache row j*n + s
     const int r0 = dr.klo + split * dr.per;
     if (r0 >= dr.kvlen) return;  // the combine reads the splits that have rows
     const int r1 = min(dr.kvlen, r0 + dr.per);
     const int nt = (r1 - r0 + kTile - 1) / kTile;
+    const Mask mk(g, dr, l32);
 
-    const size_t cslice = (size_t)g.n * g.Lcap * g.Hkv * D;  // one sequence's cache
-    const rsrc_t rk = make_rsrc(kc + pr.b * cslice, (uint32_t)(cslice * 2));
-    const rsrc_t rv = make_rsrc(vc + pr.b * cslice, (uint32_t)(cslice * 2));
+    // the sequence's cached rows; rows past the context are out of range and load zeros
+    const size_t cslice = (size_t)g.n * g.Lcap * g.Hkv * D;
+    const uint32_t range = (uint32_t)((size_t)(dr.ctx + 1) * g.n * g.Hkv * D * 2);
+    const rsrc_t rk = make_rsrc(kc + pr.b * cslice, range);
+    const rsrc_t rv = make_rsrc(vc + pr.b * cslice, range);
     const uint32_t kstride = (uint32_t)(g.mode == 0 ? g.n : 1) * g.Hkv * D * 2;
     const uint32_t kbase = (uint32_t)((g.mode == 0 ? pr.s : 0) * g.Hkv + pr.hk) * D * 2;
 
-    char *const ring = smem + wave * S * STAGE;
-    char *const qtile = smem + RING;
+    char *const ktile = smem + wave * 2 * T::BYTES, *const vtile = ktile + T::BYTES;
+    char *const qtile = smem + TILES;
     const auto plan = T::template dma_plan<1>(kbase, kstride, 0, lane);
-    // tile t of the split into stage t / NW % S; rows past the context load zeros.  Whole
-    // lines read once: streaming loads, unless another head chunk reads the rows too or, at D=32,
-    // the other half of the line is another head's row (16 x 2597 rows of 3 streams, 64/8 heads
-    // of 32: 50.6 us streaming, 47.3 cached; at D=64 177 streaming and 195 cached).
-    auto issue = [&](int t, char *st) __attribute__((always_inline)) {
-        const int row0 = r0 + t * kTile;
-        const uint32_t off = (uint32_t)row0 * kstride;
-        const bool whole = row0 + kTile <= dr.kvlen, once = D > 32 && g.ngc == 1;
+    // K or V rows of tile t of the split to st; tiles past the last one load zeros, so that the
+    // loads in flight can be counted.
+    auto issue = [&](rsrc_t rs, int t, char *st) __attribute__((always_inline)) {
+        const uint32_t off = t < nt ? (uint32_t)(r0 + t * kTile) * kstride : kOob;
 #pragma unroll
-        for (int i = 0; i < T::INSTR; ++i) {
-            uint32_t x = plan.voff[i] + off;
-            if (!whole && row0 + (i * 64 + lane) / T::CH >= dr.kvlen) x = kOob;
-            if (once) {
-                dma_lds16_nt(rk, st + i * 1024, x);
-                dma_lds16_nt(rv, st + T::BYTES + i * 1024, x);
-            } else {
-                dma_lds16(rk, st + i * 1024, x);
-                dma_lds16(rv, st + T::BYTES + i * 1024, x);
-            }
+        for (int i = 0; i < LOADS; ++i) {
+            if constexpr (ONCE)
+                dma_lds16_nt(rs, st + i * 1024, plan.voff[i] + off);
+            else
+                dma_lds16(rs, st + i * 1024, plan.voff[i] + off);
         }
     };
 
     // The 32 query slots (column l32 of the MFMA results is slot l32), shared by the waves, and
-    // behind them the first tile.
+    // behind them the first tiles.
     const int nslot = g.nslot;
     {
         const rsrc_t rq = make_rsrc(q, (uint32_t)((size_t)g.B * g.n * g.Hq * D * 2));
 #pragma unroll
-        for (int i = wave; i < T::INSTR; i += NW) {
+        for (int i = wave; i < LOADS; i += NW) {
             const int x = i * 64 + lane, slot = x / T::CH, c = (x % T::CH) ^ T::swz(slot);
             const int st = g.mode == 0 ? pr.s : slot / g.gchunk;
             const int h = pr.hk * g.G + pr.gc * g.gchunk + (g.mode == 0 ? slot : slot % g.gchunk);
@@ -124,16 +136,12 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
                       slot < nslot ? (uint32_t)((((size_t)pr.b * g.n + st) * g.Hq + h) * D * 2) + c * 16 : kOob);
         }
     }
-    int t = wave;
-    if (t < nt) {
-        issue(t, ring);
-        wait_loads_le<LOADS>();
-    } else {
-        wait_loads_le<0>();
-    }
+    issue(rk, wave, ktile);
+    issue(rv, wave, vtile);
     uint32_t kro[KS], vto[DB][2];
     T::row_offsets(l32, hi, kro);
     T::tr_offsets(lane, vto);
+    wait_loads_le<2 * LOADS>();
     lds_barrier();
     bf16x8 qr[KS];
 #pragma unroll
@@ -144,38 +152,38 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
 #pragma unroll
     for (int db = 0; db < DB; ++db) oacc[db] = f32x16{};
     const float c2 = g.scale_log2;
-    const int qp = pos0 + (g.mode == 0 ? 0 : l32 / g.gchunk);  // my query's key coordinate
-    for (int i = 0; t < nt; ++i, t += NW) {
-        char *const st = ring + i % S * STAGE;
-        if (S == 2 && t + NW < nt) {
-            issue(t + NW, ring + (i + 1) % S * STAGE);
-            wait_loads_le<LOADS>();
-        } else {
-            wait_loads_le<0>();
-        }
+    // K of the wave's next tile is loaded once the scores of this one are formed, its V once this
+    // one's product is: what is waited for has landed when only the tile issued after it is in
+    // flight.
+    for (int t = wave; t < nt; t += NW) {
         const int kb = r0 + t * kTile;
-        // S^T = K Q^T, then the mask: a row is visible if it exists and, for cross-stream
-        // layers, lies at or before my query and within the window
+        wait_loads_le<LOADS>();
+        bf16x8 a[KS];
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) a[kk] = T::row_at(ktile, kro[kk], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        // S^T = K Q^T
         f32x16 sc = {};
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) sc = mfma32(T::row_at(st, kro[kk], 0), qr[kk], sc);
+        for (int kk = 0; kk < KS; ++kk) sc = mfma32(a[kk], qr[kk], sc);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue(rk, t + NW, ktile);
         mfma_settle();
-        const int last = kb + kTile - 1;
-        const bool masked = last >= dr.kvlen ||
-                            (g.mode != 0 && (last > pos0 || pos0 + g.n - 1 - kb >= g.window));
-        float mx = -INFINITY;
+        float x[16], mx = -INFINITY;
+        if (mk.some(kb)) {
+            const int lim = mk.limit - kb - 4 * hi, lo = mk.below - kb - 4 * hi;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float x = sc[r] * c2;
-            if (masked) {
-                const int j = kb + 8 * (r >> 2) + 4 * hi + (r & 3);
-                bool vis = j < dr.kvlen;
-                if (g.mode != 0) vis = vis && j <= qp && qp - j < g.window;
-                x = vis ? x : -INFINITY;
+            for (int r = 0; r < 16; ++r) {
+                const int j = 8 * (r >> 2) + (r & 3);
+                x[r] = ((j > lim) | (j <= lo)) ? -INFINITY : sc[r] * c2;
             }
-            sc[r] = x;
-            mx = fmaxf(mx, x);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[r] = sc[r] * c2;
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, x[r]);
         const float mn = fmaxf(m, max_xor32(mx));
         if (__any(mn > m)) {
             const float alpha = mn == m ? 1.f : fast_exp2(m - mn);
@@ -192,23 +200,30 @@ __global__ __launch_bounds__(NW * 64, 1) void sfa_decode_partial_kernel(
             uint32_t w[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                w[e] = pack_bf16(fast_exp2(sc[h * 8 + 2 * e] - me), fast_exp2(sc[h * 8 + 2 * e + 1] - me));
+                w[e] = pack_bf16(fast_exp2(x[h * 8 + 2 * e] - me), fast_exp2(x[h * 8 + 2 * e + 1] - me));
                 // the sum adds the bf16 weights that the P V product uses
                 lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[e]), ones, lsum, false);
             }
             pb[h] = __builtin_bit_cast(bf16x8, u32x4{w[0], w[1], w[2], w[3]});
         }
         // O^T (dims x slots) += V^T P^T
+        wait_loads_le<LOADS>();
+        bf16x8 b[DB][2];
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-                oacc[db] = mfma32(T::tr_at(st + T::BYTES, vto[db], kk), pb[kk], oacc[db]);
-        // this stage is loaded again in the next step (or now): its reads have completed
+            for (int db = 0; db < DB; ++db) b[db][kk] = T::tr_at(vtile, vto[db], kk);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) oacc[db] = mfma32(b[db][kk], pb[kk], oacc[db]);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (S == 1 && t + NW < nt) issue(t + NW, ring);
+        issue(rv, t + NW, vtile);
+        mfma_settle();
     }
+    wait_loads_le<0>();  // nothing may write the tiles any more
     mfma_settle();
     lsum = sum_xor32(lsum);
 
@@ -326,14 +341,10 @@ DecGeom make_dec_geom(int B, int Lcap, int n, int Hq, int Hkv, int D, int mode, 
     g.nchunk = (int)((rows + kDecChunk - 1) / kDecChunk);
     g.problems = B * Hkv * g.ngc * (mode == 0 ? n : 1);
     g.nslot = g.gchunk * per_head;
-    g.heads = dec_heads(g.problems, D, Hkv);
     // a local layer's rows span at most the window, the other streams of the token and the
     // rounding down to a tile
     const int64_t span = mode == 2 ? (int64_t)window + n + kTile : INT32_MAX;
-    const int64_t cap = mode == 0 ? Lcap : (int64_t)Lcap * n;
-    dec_shape(g.problems, D, (int)std::min(cap, span), g.waves, g.single);
-    // the most splits any context up to max_ctx takes
-    g.nsplit = dec_splits(g.problems, D, g.single, (int)std::min(rows, span));
+    dec_launch(g, (int)std::min(rows, span));
     return g;
 }
 
@@ -380,12 +391,20 @@ hipError_t launch_decode_bf16(const void *q, const void *kc, const void *vc, con
     auto run = [&](auto dk, const char *pname, const char *cname) {
         constexpr int DD = decltype(dk)::value;
         timing_before(pname, s);
-        if (g.waves == 8)
-            sfa_decode_partial_kernel<DD, 8, 1><<<grid, 8 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
-        else if (g.waves == 4)
-            sfa_decode_partial_kernel<DD, 4, 2><<<grid, 4 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+        auto go = [&](auto once) {
+            constexpr bool ONCE = decltype(once)::value;
+            if (g.waves == 8)
+                sfa_decode_partial_kernel<DD, 8, ONCE><<<grid, 8 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+            else
+                sfa_decode_partial_kernel<DD, 4, ONCE><<<grid, 4 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+        };
+        // Streaming loads, unless another head chunk reads the rows too or, at D=32, the other half
+        // of the line is another head's row (16 x 2597 rows of 3 streams, 64/8 heads of 32: 50.6 us
+        // streaming, 47.3 cached; at D=64 177 streaming and 195 cached).
+        if (DD > 32 && g.ngc == 1)
+            go(std::bool_constant<(DD > 32)>{});
         else
-            sfa_decode_partial_kernel<DD, 2, 2><<<grid, 2 * 64, 0, s>>>(qq, kk, vv, ctx, part, oo, lse, g);
+            go(std::false_type{});
         hipError_t e = hipGetLastError();
         timing_after(s);
         if (e != hipSuccess || g.nsplit == 1) return e;

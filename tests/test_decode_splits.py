@@ -3,8 +3,8 @@ small program over the library's own header and geometry walks head layouts, mas
 sizes, bounds and contexts (negative ones and ones past the bound among them) and asserts, for
 each, that
 
-  * the splits with rows cover a problem's visible rows once and are no more than the launch
-    has and the workspace has room for;
+  * the splits with rows cover a problem's visible rows once, are no more than the launch has
+    and the workspace has room for, and do not depend on capacity or bound;
   * a context outside [0, bound] counts as the nearest one inside, so that no index leaves the
     grid, the workspace or the cache;
   * every (problem, split) has exactly one workgroup, neighbouring heads that share cache lines
@@ -57,6 +57,7 @@ int main()
                             if (mode != 2 && window != 1) continue;
                             for (int bound : bounds) {
                                 const DecGeom g = make_dec_geom(B, bound + 1, n, h[0], h[1], D, mode, window, 1.f, bound);
+                                const DecGeom big = make_dec_geom(B, 50001, n, h[0], h[1], D, mode, window, 1.f, 50000);
                                 int ctx = 0;
                                 CHECK(g.nsplit >= 1 && g.nsplit <= g.nchunk);
                                 for (int c : {-7, 0, 1, 30, 100, 255, 300, 383, 500, 640, 800, 1024, 1500, 2047, 2100, 4096, 9000, 39999, 60000}) {
@@ -72,6 +73,9 @@ int main()
                                     } else {
                                         CHECK(r.klo == 0);
                                     }
+                                    const DecRows rb = dec_rows(big, r.ctx);
+                                    CHECK(rb.per == r.per && rb.klo == r.klo && rb.kvlen == r.kvlen);
+                                    CHECK(g.waves == big.waves);
                                     ++cases;
                                 }
                             }
