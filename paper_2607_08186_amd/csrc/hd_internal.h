@@ -188,6 +188,47 @@ __host__ __device__ inline void dkdv_sweep(const SfaGeom &g, int kt, int &first,
     end = (int)(e < nqt ? e : nqt);
 }
 
+// Small grids of the forward and of dQ take blocks of 128 query rows whose key steps two groups
+// of waves share, instead of 256 rows: half the steps per block, twice the blocks.  At D >= 64 a
+// CU holds one such block.  While every block has a CU that is a gain (D=128, forward / dQ,
+// without -> with: 128 blocks of 256 rows, L=300: 18.6 -> 14.6 us / 14.4 -> 11.1; 144, which make
+// 216 of 128 rows: 17.8 -> 14.1 / 13.9 -> 11.4).  Past kCus a second round of blocks
+// begins, and costs about what 500 keys take before it has computed anything: 192 blocks of
+// L=250 lose (20.0 -> 24.5 / 15.4 -> 18.1), as do 192 of a window of 400 (31.8 -> 35.2 / 20.7 ->
+// 25.0), while under long causal sweeps the second round is the short rows' and fills in behind
+// the long ones' (192 blocks, L=800: 28.5 -> 27.5 / 22.6 -> 20.2; L=2000: 51.8 -> 41.2 / 42.4 ->
+// 33.0).  At D=32 two blocks fit a CU and none of these loses.
+constexpr int kSplitMax = 192;     // 256-row blocks: with 256, L=300, D=128, the forward is 24 us for 20
+constexpr int kSplitSweep = 750;   // keys of the longest block, from which a second round pays
+
+inline bool split_fits(const SfaGeom &g)  // as many 128-row blocks as the chip holds at once
+{
+    return g.D == 32 || (int64_t)((g.qlen + 127) / 128) * g.B * g.Hq * g.streams <= kCus;
+}
+
+inline bool split_grid(const SfaGeom &g)
+{
+    return (int64_t)((g.qlen + 255) / 256) * g.B * g.Hq * g.streams <= kSplitMax;
+}
+
+// A final-stream block's waves take strided rows, so that all of them run the whole sweep: there
+// the split always pays (192 blocks of 250 rows, n=4: 51.0 -> 44.1; 8 of 300 rows, window 20:
+// 46.4 -> 19.8).  One key tile per group has nothing to share: L=120, D=128, 8 blocks 11.1 -> 11.9.
+inline bool fwd_split(const SfaGeom &g)
+{
+    if (!split_grid(g)) return false;
+    return g.strided_waves ||
+           (g.len > 128 && (split_fits(g) || (g.len < g.window ? g.len : g.window) >= kSplitSweep));
+}
+
+// dQ's sweeps are shorter than the forward's, and under a window all alike: a second round pays
+// from rows, not keys (192 final-stream blocks of 250 rows, n=4: 26.7 -> 29.3; of 800, n=2: 34.0 ->
+// 26.5; 192 of a window of 1000, D=64: 23.8 -> 26.5).
+inline bool dq_split(const SfaGeom &g)
+{
+    return split_grid(g) && (split_fits(g) || (g.window >= g.len && g.qlen >= kSplitSweep));
+}
+
 // Small dK/dV grids (fewer than kSplitGrid workgroups, i.e. under two per CU on
 // MI355X) split the longest key-tile sweeps over two workgroups each, which run at the
 // same time and leave fp32 partials for a combine pass; without it the step lasts as

@@ -661,14 +661,11 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
 }
 
 // Small grids.  dK/dV with at most kNarrowItems work items of 128 keys takes workgroups of 64
-// keys and four waves: twice as many, each with its SIMDs to itself (96 items at D=128: 42 ->
-// 37 us, 24 items 57 -> 50; but 176 items 28 -> 32, which no longer fit one per CU).  dQ with
-// at most kDqSplitMax 256-row blocks takes 128-row blocks whose key steps the wave groups
-// split (32 blocks at D=128, N=1000: 26 -> 19 us; 64 of L=1000: 26 -> 19; 264 final-stream blocks
-// 28 -> 30).  The choice for dQ looks at all of the problem's rows, not at a query
-// band's, so that dQ does not depend on the workspace.
+// keys and four waves: twice as many, each with its SIMDs to itself (D=128: 96 items 42 -> 37 us,
+// 128 of L=250 36.2 -> 31.1, 24 items 57 -> 50; but 176 items 28 -> 32, which no longer fit one per
+// CU).  The choice for dQ looks at all of the problem's rows, not at a query band's, so that dQ
+// does not depend on the workspace.
 constexpr int kNarrowItems = 128;
-constexpr int kDqSplitMax = 192;
 
 template <int D>
 hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o,
@@ -747,9 +744,8 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         }
         const int nrb = (min(qb * kDsRows, g.qlen) + kRowsPerWg - 1) / kRowsPerWg - qa / kBandUnit;
         const int64_t wgs = nrb * nprob_q;
-        const bool dq_split = (int64_t)((g.qlen + kRowsPerWg - 1) / kRowsPerWg) * nprob_q <= kDqSplitMax;
         timing_before(dq_name, s);
-        if (dq_split) {
+        if (dq_split(g)) {
             const int nhb = (min(qb * kDsRows, g.qlen) + kRowsPerWg / 2 - 1) / (kRowsPerWg / 2) - qa / kBandUnit * 2;
             sfa_dq_bf16_kernel<D, 64, 2, true><<<(unsigned)(nhb * nprob_q), kDqWaves * 64, 0, s>>>(k, ds, dq, g, band_tiles, bd);
         } else if (wgs > (int64_t)per_cu * cus)

@@ -35,10 +35,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // FINAL: final-stream layer (query row i at key coordinate i*n + n - 1, strided wave
 // rows); otherwise query row i is key coordinate i and waves take consecutive rows.
 // Block shapes.  kPlain: 256 rows, one workgroup per CU at D >= 64.  kShared (D = 64): the same
-// held to 128 registers, so that two workgroups share a CU.  kSplit: a block holds 128 rows, both groups of waves own the same ones (wave w
-// and w + 4 rows 32w ..) and take every second key tile each, group B the odd ones, through
-// rings of their own; at the end group A adds group B's part, scaled to the common
-// reference.  Half the phases per block and twice the blocks.
+// held to 128 registers, so that two workgroups share a CU.  kSplit: a block holds 128 rows,
+// both groups of waves own the same ones (wave w and w + 4 rows 32w ..) and take every second
+// key tile each, group B the odd ones, through rings of their own; at the end group A adds
+// group B's part, scaled to the common reference.  Half the phases per block, twice the blocks.
 enum Shape { kPlain, kShared, kSplit };
 
 template <int D, bool FINAL, Shape SHAPE>
@@ -369,18 +369,15 @@ __global__ __launch_bounds__((kWaves * 64), (SHAPE == kShared ? 4 : 2)) void sfa
     }
 }
 
-// The block shape for a grid of `wgs` 256-row blocks (256 CUs):
-//   up to kSplitMax of them, the split one: it halves the longest block where CUs would idle
-//     (D=128, 32 blocks of 2000 rows: 31 -> 22 us; 96 blocks of 6124 rows: 127 -> 80; 192
-//     blocks at D=64: 30 -> 22; but 256 short blocks, L=302: 20 -> 24);
-//   at D=64 above kPlainMax, two workgroups per CU: each one's softmax and barriers overlap the
-//     other's MFMAs (768 blocks: 115 -> 101 us, 9216 blocks: 1116 -> 985), while a grid that
-//     would be resident at once then puts long causal blocks on one CU (288 blocks: 80 -> 87).
-constexpr int kSplitMax = 192;
+// The block shape for a grid of `wgs` 256-row blocks: split where fwd_split says so; at D=64
+// above kPlainMax, two workgroups per CU: each one's softmax and barriers overlap the other's
+// MFMAs (768 blocks: 115 -> 101 us, 9216 blocks: 1116 -> 985; 592 of L=500 37.3 -> 33.7, 544 of a
+// window of 100 39.2 -> 33.4, 576 final-stream ones 140 -> 125), while a grid that would be
+// resident at once then puts long causal blocks on one CU (288 blocks: 80 -> 87).
 constexpr int kPlainMax = 512;
-Shape fwd_shape(int D, int64_t wgs)
+Shape fwd_shape(const SfaGeom &g, int64_t wgs)
 {
-    return wgs <= kSplitMax ? kSplit : D == 64 && wgs > kPlainMax ? kShared : kPlain;
+    return fwd_split(g) ? kSplit : g.D == 64 && wgs > kPlainMax ? kShared : kPlain;
 }
 
 }  // namespace
@@ -390,7 +387,7 @@ hipError_t launch_fwd_bf16(const void *q, const void *k, const void *v, void *o,
 {
     const int nprob = g.B * g.Hq * g.streams;
     const int wgs = (g.qlen + kBM - 1) / kBM * nprob;
-    const Shape shape = fwd_shape(g.D, wgs);
+    const Shape shape = fwd_shape(g, wgs);
     const dim3 grid(shape == kSplit ? (g.qlen + kBM / 2 - 1) / (kBM / 2) * nprob : wgs), block(kWaves * 64);
     const bf16 *qq = static_cast<const bf16 *>(q), *kk = static_cast<const bf16 *>(k),
                *vv = static_cast<const bf16 *>(v);
