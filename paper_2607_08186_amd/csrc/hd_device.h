@@ -68,9 +68,10 @@ __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
 // Lets every MFMA issued so far finish (24 wait states; a 32x32x16 bf16 result is readable
 // after 11, a 16x16x4 fp32 one after 10).  The compiler places these wait states itself, but
 // where a branch separates an MFMA from the first read of its result it has counted them
-// along the longer path into the join only, and the shorter one then read the last result
-// registers too early.  So kernels put this (or `pin` the result, in the MFMA's own block)
-// before such a branch or right after it.
+// along the longer path into the join only, and the shorter one (a tile without a mask) then
+// read the last result registers too early.  So every kernel puts this, or `pin`s the result
+// in the MFMA's own block, between a product and a read that a branch or the end of a loop
+// separates from it, also where a barrier lies between them today: 24 cycles per block.
 __device__ inline void mfma_settle()
 {
     __builtin_amdgcn_sched_barrier(0);

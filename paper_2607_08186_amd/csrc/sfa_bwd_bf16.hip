@@ -376,6 +376,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
         if (it + 1 < iters) step(it + 1, std::integral_constant<int, 1>{});
     }
 
+    mfma_settle();
     // sum the two query halves: waves KW.. park their partials in LDS (one 16-byte
     // slot per lane and register quad), waves 0..KW-1 add them and write dK/dV
     f32x4 *park = reinterpret_cast<f32x4 *>(smem) + kw * (2 * DB * 4 * 64);
@@ -629,8 +630,8 @@ __global__ __launch_bounds__(kDqWaves * 64, 1) void sfa_dq_bf16_kernel(
         }
         lds_barrier();
     }
+    mfma_settle();
     if constexpr (SPLIT) {
-        mfma_settle();
         float *part = reinterpret_cast<float *>(rings) + gwave * (DB * 16 * 64) + lane;
         if (group == 1) {
 #pragma unroll

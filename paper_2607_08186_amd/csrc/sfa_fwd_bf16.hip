@@ -325,10 +325,10 @@ __global__ __launch_bounds__((kWaves * 64), (SHAPE == kShared ? 4 : 2)) void sfa
         bar();
     }
 
+    mfma_settle();
     float l = sum_xor32(lsum0 + lsum1);
     if constexpr (SPLIT) {
         // every wave has passed the last barrier: the rings are free
-        mfma_settle();
         float *part = reinterpret_cast<float *>(kv) + rw * (16 * DB + 2) * 64 + lane;
         if (group == 1) {
 #pragma unroll

@@ -62,6 +62,22 @@ def test_decode_context_outside_the_bound(mode, w):
     assert np.all(np.isfinite(a[0]))
 
 
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("rows", [32, 64, 320, 31, 60])
+def test_decode_last_rows_of_a_tile(rows, D):
+    """All of a query's weight lies on one of the last rows of the last tile, whole (no mask, the
+    shortest way from the scores' product to their first read) or ragged: those rows' scores
+    are the last registers that the product writes."""
+    B, n, Hq, Hkv, scale = 4, 1, 4, 1, D ** -0.5
+    ins = _inputs(synth.seed_for("decode-last", rows, D), B, rows, n, Hq, Hkv, D)
+    for b, back in enumerate((0, 1, 4, 5)):
+        x = 8 * synth.bf16_bits_to_f32(ins["q"][b].reshape(-1)[:D])
+        ins["k"][b, rows - 1 - back, 0] = synth.to_bf16_bits(x)
+    o, lse = _run(ins, [rows - 1] * B, MIX, 0)
+    ro, rl = oracle.sfa_decode(ins["q"], ins["k"], ins["v"], [rows - 1] * B, n=n, mode=MIX, scale=scale, window=0)
+    G.assert_close_fwd(o, lse, ro, rl, "bf16", str((rows, D)))
+
+
 # B, n, Hq, Hkv, D, mode, window, contexts: problems on both sides of the lines of the rule
 SHAPES = [
     (2, 4, 8, 4, 128, INTRA, 0, [639, 500]),            # 32 problems: whole, eight waves
