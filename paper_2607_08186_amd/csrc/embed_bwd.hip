@@ -347,6 +347,15 @@ __global__ __launch_bounds__(kThreads) void mid_hist_kernel(const uint32_t *__re
     for (int d = threadIdx.x; d < kMidDigits; d += kThreads) hist[(int64_t)blockIdx.x * kMidDigits + d] = h[d];
 }
 
+// Orders the LDS accesses of one wave's lanes before it against those after it (no instruction:
+// a wave's LDS accesses run in order, the compiler's order is what it holds).
+__device__ inline void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 __global__ __launch_bounds__(kThreads) void mid_scatter_kernel(
     const uint32_t *__restrict__ keys, const int32_t *__restrict__ vals, const int32_t *__restrict__ ids,
     int M, int64_t V, int shift, const int *__restrict__ hist, uint32_t *__restrict__ keys_out,
@@ -398,9 +407,9 @@ __global__ __launch_bounds__(kThreads) void mid_scatter_kernel(
         const int below = __popcll(peers & (((uint64_t)1 << lane) - 1));
         rank[j] = 0;
         if (ok) rank[j] = wh[wave][d] + below;
-        __builtin_amdgcn_wave_barrier();  // every lane has read before the first peer adds
+        wave_fence();  // every lane has read before the first peer adds
         if (ok && below == 0) wh[wave][d] += __popcll(peers);
-        __builtin_amdgcn_wave_barrier();
+        wave_fence();
     }
     __syncthreads();
     // wh becomes the position of the wave's first key of each digit
