@@ -71,8 +71,10 @@ CASES = [
     (1, 5000, 2, 1 << 20, 8, "bf16"),
     (1, 300, 2, 2 ** 31 - 1, 8, "bf16"),  # ids over the whole int32 range: four passes
     (1, 1, 3, 10, 32, "bf16"),           # a single token
-    (1, 16384, 2, 151936, 16, "bf16"),   # the largest batch of the one-pass counting sort
-    (1, 16385, 2, 151936, 16, "bf16"),   # the smallest one of the radix sort
+    (1, 8192, 2, 151936, 16, "bf16"),    # the largest batch of the one-pass counting sort
+    (1, 8193, 2, 151936, 16, "bf16"),    # the smallest one of the 9-bit radix sort
+    (1, 16384, 2, 151936, 16, "bf16"),   # 16 whole 1024-key blocks of it
+    (1, 16385, 2, 151936, 16, "bf16"),   # and one key more
     (2, 8500, 1, 1000, 2056, "f32"),     # radix sort with heavy repeats; rows of 1+ chunks
 ]
 
@@ -92,10 +94,10 @@ def test_expand_bwd_out_of_range_ids_are_dropped():
     _check(ids, _dout(seed + 1, B, n * L, Dm, "bf16"), V)
 
 
-@pytest.mark.parametrize("V", [(1 << 18) - 1, 1 << 18])
+@pytest.mark.parametrize("V", [(1 << 18) - 1, 1 << 18, (1 << 19) - 1, 1 << 19])
 def test_expand_bwd_sort_key_packing_boundary(V):
-    """The counting sort packs (id, token) into one 32-bit word while every key fits 18
-    bits (V < 2^18, the out-of-range marker V included) and compares the two parts
+    """The counting sort packs (id, token) into one 32-bit word while every key fits 19
+    bits (V < 2^19, the out-of-range marker V included) and compares the two parts
     otherwise: ids near the top of [0, V), repeats and out-of-range ids on both sides of
     that boundary."""
     B, L, n, Dm = 2, 1500, 2, 16

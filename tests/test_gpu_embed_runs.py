@@ -1,6 +1,7 @@
 """Expansion backward where its row-wise work split can go wrong: runs of equal ids at and
 around the 4 and 16 rows a wave loads at once and the 16 rows of a run that four waves
-split, runs that start and end at the edges of those groups, rows of odd widths, and the token counts where the sort changes.
+split, runs that start and end at the edges of those groups, rows of odd widths, and the token
+counts where the sort changes.
 
 Distinct ids must be bit-exact, rows within the rounding bound of an fp32 sum in token
 order (see test_gpu_embed_bwd)."""
@@ -41,10 +42,12 @@ def test_run_lengths(name, Dm, dtype, bad):
 
 
 @pytest.mark.parametrize("M,V", [(8192, 2 ** 19 - 1), (8192, 2 ** 19), (8193, 151936), (9216, 511), (18433, 512), (20480, 2 ** 18),
-                                 (40000, 2 ** 27 + 5), (131072, 3000), (131073, 3000)])
+                                 (40000, 2 ** 27 + 5), (131072, 3000), (131073, 3000), (131073, 151936),
+                                 (131073, 2 ** 27 + 5)])
 def test_sort_sizes(M, V):
     """Counting sort up to 8192 tokens (packed keys for V < 2^19), 9-bit digits up to 131072 (one to four passes, by
-    V), the device-wide scans beyond; a tenth of the ids outside [0, V)."""
+    V), 8-bit ones with device-wide scans beyond (two, three and four passes: results in either buffer pair); a
+    tenth of the ids outside [0, V)."""
     seed = synth.seed_for("embed_sort_sizes", M, V)
     rng = np.random.default_rng(seed)
     ids = (V * rng.random(M) ** 3).astype(np.int64)
