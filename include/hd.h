@@ -23,6 +23,11 @@
  *     decode caches) must stay below 2^31 bytes (32-bit offsets inside the kernels);
  *     larger inputs are rejected with HD_ERR_INVALID_ARG.  The expansion, its
  *     gradient and the final-stream gather state their own limits.
+ *   - Every call is deterministic: the same arguments give the same bits.  A sequence's
+ *     attention results do not depend on what the other sequences of a batch hold, but
+ *     the order in which a row's terms are added follows the size of the call (B, heads,
+ *     lengths), which decides how the work is cut to fill the GPU: with another batch
+ *     size or head count the last bits may differ, forward, backward and decode.
  *   - Calls are thread-safe with respect to each other; calls that write the same
  *     output buffers on overlapping streams race, as with any kernel.
  */
@@ -337,8 +342,12 @@ hd_status_t hd_sfa_bwd_final(const void *q, const void *k, const void *v, const 
  * max_ctx_tokens  host bound on ctx_tokens (sizes the launch and the workspace), < Lcap.
  * o               device bf16 [B][n][Hq][D];  lse  device float [B][Hq][n] (natural log).
  * window          the local window (HD_SFA_LOCAL, >= 1); ignored by the other modes.
- * workspace       device, 256-byte aligned, hd_sfa_decode_workspace_bytes(...) bytes:
- *                 fp32 partial results per 256 cached rows.
+ * workspace       device, 256-byte aligned, hd_sfa_decode_workspace_bytes(...) bytes: room
+ *                 for one fp32 partial result per problem and 256 cached rows under the
+ *                 bound (a call uses as many as it splits a problem into).
+ * A sequence's result depends on its own rows, and in its last bits on B and the heads: its
+ * rows are split over more workgroups when the call has few problems.  It does not depend on
+ * Lcap, on the bound or on the other sequences' contexts.
  * Errors: INVALID_ARG for null or misaligned pointers, sizes <= 0, Hq % Hkv != 0, a bad
  *         mode, window or scale, max_ctx_tokens outside [0, Lcap), oversize tensors or a
  *         short workspace; UNSUPPORTED for fp32 or D not in {32, 64, 128}.

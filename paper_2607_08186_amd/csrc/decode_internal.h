@@ -26,8 +26,8 @@ struct DecGeom {
 // Split of a problem's cached rows over workgroups.  It follows from the number of problems,
 // the head dim and the sequence's own rows, and neither from the cache's capacity nor from the
 // bound on the contexts: these change no bit of a result, and no short context pays for a large
-// cache (D=128, launch to launch, 32 to 256 problems of 100 to 1000 rows in a cache of 4096: 10.7 to 22
-// us, as in a tight one; shaped by the capacity they took 14.7 to 28.6).
+// cache (D=128, launch to launch, 32 to 256 problems of 100 to 1000 rows in a cache of 4096:
+// 10.7 to 22 us, as in a tight one; shaped by the capacity they took 14.7 to 28.6).
 //   Workgroups: eight waves, one workgroup per CU, up to 256 problems at D=128; half of that each
 //     beyond (256 CUs; 264 problems of 700 rows 23.6 -> 22.7 us) and, where a tile is half the
 //     bytes or less, from 65 problems on (D=64: 96 of 2000 rows 18.9 -> 15.5).

@@ -38,12 +38,10 @@ constexpr int kItems = 8;
 constexpr int kChunk = kThreads * kItems;  // keys per block in the scan and sort kernels
 constexpr int kWaves = kThreads / 64;
 
-// Exclusive scan of one int per thread across a workgroup of W waves; *total gets the
-// sum.  `sh` is LDS scratch of W + 1 ints.
-template <int W = kWaves>
+// Exclusive scan of one int per thread across the workgroup; *total gets the sum.  `sh` is
+// LDS scratch of kWaves + 1 ints.
 __device__ inline int block_exclusive_scan(int x, int *total, int *sh)
 {
-    constexpr int kWaves = W;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int v = x;
 #pragma unroll
@@ -269,7 +267,7 @@ __global__ __launch_bounds__(kRankTokens * kRankChunks) void rank_sort_kernel(
 {
     __shared__ uint32_t sk[kSmallSortMax];
     __shared__ int cnt[kRankChunks][kRankTokens];
-    // all of a thread's ids in flight at once (64 at kSmallSortMax tokens): buffer loads
+    // all of a thread's ids in flight at once (32 at kSmallSortMax tokens): buffer loads
     // past the M ids return 0 instead of being branched around, so that no load waits
     // for the one before it
     constexpr int kFill = kSmallSortMax / (kRankTokens * kRankChunks);
@@ -318,7 +316,7 @@ __global__ __launch_bounds__(kRankTokens * kRankChunks) void rank_sort_kernel(
 // (digit counts, scatter).  A workgroup ranks 1024 keys: per wave and 64 keys the lanes with
 // the same digit find each other by nine ballots, and a running count per (wave, digit) in
 // LDS ranks them stably.  Every workgroup adds up the digit counts of all 1024-key blocks
-// itself (they are few: 64 at kMidSortMax), which saves the scan launches.  32768 text-like
+// itself (they are few: 128 at kMidSortMax), which saves the scan launches.  32768 text-like
 // ids below 151936: 35 us with the run indices, 103 us in the 26 launches of the
 // general sort.  (Counting the next pass's digits inside the scatter with global atomics
 // saves a launch but queues on the few addresses that frequent ids share: 48 us.)

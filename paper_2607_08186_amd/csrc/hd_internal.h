@@ -198,7 +198,7 @@ __host__ __device__ inline void dkdv_sweep(const SfaGeom &g, int kt, int &first,
 // 25.0), while under long causal sweeps the second round is the short rows' and fills in behind
 // the long ones' (192 blocks, L=800: 28.5 -> 27.5 / 22.6 -> 20.2; L=2000: 51.8 -> 41.2 / 42.4 ->
 // 33.0).  At D=32 two blocks fit a CU and none of these loses.
-constexpr int kSplitMax = 192;     // 256-row blocks: with 256, L=300, D=128, the forward is 24 us for 20
+constexpr int kSplitMax = 192;     // blocks of 256 rows; 256 of L=300 at D=128 lose (20 -> 24 us)
 constexpr int kSplitSweep = 750;   // keys of the longest block, from which a second round pays
 
 inline bool split_fits(const SfaGeom &g)  // as many 128-row blocks as the chip holds at once
@@ -372,7 +372,7 @@ struct QBand {
 //   bf16 path only, one pass: the dS tiles of every problem (b, hq[, s]),
 //     problem-major (ds, total);
 //   bf16 path only, one pass with split sweeps (dkdv_splits > 0): after the dS tiles,
-//     the fp32 partials of the two halves of every split sweep (split), laid out
+//     the fp32 partials of the two parts of every split sweep (split), laid out
 //     [half][dK, dV][key problem][split keys][D];
 //   bf16 path only, in query bands: the fp32 dK and dV partials, then the dS tiles of
 //     one band (part_k, part_v, ds_banded); the smallest workspace holds the dS tiles of

@@ -7,8 +7,8 @@
 //   dV = P^T dO,  dK = scale dS^T Q,  dQ = scale dS K,   Delta = rowsum(dO * O).
 // Three deterministic kernels (no atomics):
 //   stats: -Delta and -lse/scale of every query row.
-//   dK/dV: a workgroup owns 128 keys of one (b, kv-head[, stream]) problem (K and V
-//          resident in LDS), 32 per pair of waves, and sweeps the query tiles that see
+//   dK/dV: a workgroup owns 128 keys (64 on small grids) of one (b, kv-head[, stream])
+//          problem (K and V resident in LDS), 32 per pair of waves, and sweeps the query tiles that see
 //          them for every query head of the group, so the grouped-query sum happens in
 //          registers; the two waves of a pair split each query tile and add their
 //          partials once at the end.  Scores are formed as
@@ -20,9 +20,9 @@
 //          per wave, one row per lane) and streams the dS tiles and key rows at or
 //          below the diagonal through an LDS ring (32 keys x 2 stages, several
 //          workgroups per CU, unless that would make the whole grid resident at
-//          once; then 64 keys x 3 stages; small grids 128-row blocks, see below), dQ^T += K^T dS^T with
-//          both operands read transposed from LDS.  No S or dP is recomputed, so this
-//          pass is bound by the dS reads from HBM.
+//          once; then 64 keys x 3 stages; small grids take blocks of 128 rows), dQ^T +=
+//          K^T dS^T with both operands read transposed from LDS.  No S or dP is
+//          recomputed, so this pass is bound by the dS reads from HBM.
 // All tiles move HBM -> LDS through direct-to-LDS buffer loads.
 #include <atomic>
 #include <type_traits>
@@ -185,7 +185,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     const int nqt = max(0, qt_end - qt_first);
     const int iters = g.G * nqt;
 
-    // this workgroup's 128 keys and values, resident in LDS for the whole sweep
+    // this workgroup's keys and values, resident in LDS for the whole sweep
 #pragma unroll
     for (int t = 0; t < kKeysPerWg / kRows; ++t) {
         T::load(kvt + t * T::BYTES, rk, kbase, kstride, k0 + t * kRows, g.len, wave, kDkdvWaves, lane);
@@ -393,7 +393,7 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     }
     __syncthreads();
     if (half >= 0 && qb == 0 && key < g.len) {
-        // one half of a split sweep: fp32 sums [half][dK, dV][problem][key][D]
+        // one part of a split sweep: fp32 sums [part][dK, dV][problem][key][D]
         const size_t slice = (size_t)nsplit * kMaxKeysPerWg * D;
         float *pk = split + ((size_t)(half * 2) * nprob + prob) * slice + (size_t)key * D;
         float *pv = split + ((size_t)(half * 2 + 1) * nprob + prob) * slice + (size_t)key * D;
@@ -445,8 +445,8 @@ __global__ __launch_bounds__((KW * 128), 1) void sfa_dkdv_bf16_kernel(
     }
 }
 
-// dK, dV of the split key tiles: the two halves' fp32 sums added in a fixed order
-// (half 0, then half 1), scaled (dK) and rounded to bf16; four dims per thread.
+// dK, dV of the split key tiles: the two parts' fp32 sums added in a fixed order
+// (part 0, then part 1), scaled (dK) and rounded to bf16; four dims per thread.
 template <int D>
 __global__ __launch_bounds__(256) void dkdv_split_combine_kernel(const float *__restrict__ split,
                                                                  int nsplit, bf16 *__restrict__ dk,
@@ -716,7 +716,7 @@ hipError_t bwd_bf16_d(const bf16 *q, const bf16 *k, const bf16 *v, const bf16 *o
         bd.part_k = one_pass ? nullptr : reinterpret_cast<float *>(wsb + w.part_k);
         bd.part_v = one_pass ? nullptr : reinterpret_cast<float *>(wsb + w.part_v);
         const int64_t band_tiles = tiles(qa, qb);
-        // one pass only: the longest sweeps of a small grid are split in halves
+        // one pass only: the longest sweeps of a small grid are cut in two
         const SplitPlan plan = dkdv_split_plan(g, one_pass ? w.nsplit : 0);
         const int nsplit = plan.nsplit;
         float *split = reinterpret_cast<float *>(wsb + w.split);

@@ -8,9 +8,10 @@
 // bounds them is the length of the longest workgroup's serial sweep and how many CUs
 // have work.  Hence:
 //   tiles of 16 rows: a workgroup owns 16 or 32 query rows (forward, dQ) or keys (dK/dV)
-//     of one problem, and its four waves take every fourth step of the sweep over the
-//     other operand, each with its own accumulators, added in LDS in a fixed order at
-//     the end (the forward's after scaling to the waves' common row maximum);
+//     of one problem, and its waves (four; eight on 16-row tiles at D < 128) take the steps
+//     of the sweep over the other operand in turn, each with its own accumulators, added
+//     in LDS in a fixed order at the end (the forward's after scaling to the waves' common
+//     row maximum);
 //   no LDS and no barrier inside a sweep: operands go from memory (L1/L2) to registers in
 //     the layout the MFMA takes, the next step's loads issued as soon as the registers of
 //     the current one are free;
@@ -321,7 +322,7 @@ __global__ __launch_bounds__((kWavesOf<D, NQ> * 64), 1) void sfa_fwd_f32_kernel(
             for (int t = 0; t < KS; ++t)
 #pragma unroll
                 for (int i = 0; i < NQ; ++i) sc[t][i] = P::dot(kr[t], qr[i], f32x4{});
-        mfma_settle();
+            mfma_settle();
             if (j + kWaves < je) load_k(j + kWaves);
             const bool masked = kb + KT - 1 > q0 || qlast - kb >= g.window;
             auto visible = [&](int key, int i) __attribute__((always_inline)) {
