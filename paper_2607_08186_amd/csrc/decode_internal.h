@@ -40,7 +40,9 @@ struct DecGeom {
 //     cross-stream: 169 us in 2 parts, 174 in 4).
 //   Above 256 problems parts of at most `part` rows even out contexts of different lengths and
 //     the last round of workgroups (264 problems of 6000 rows at D=128: 149 us, 182 whole; 560 of
-//     4500 at D=64: 106 and 142).  So do they where `fill` is one part for 129 to 170 problems, a
+//     4500 at D=64: 106 and 142), and at D=64 above 128, where `fill` is 4 to 7 parts that do not
+//     fill the 1024 places (208 problems of 12000 rows 127 -> 116 us, of up to 12000 108 -> 98;
+//     136 of 9000 64 -> 60).  So do they where `fill` is one part for 129 to 170 problems, a
 //     third of the CUs or more idle, in long contexts (`whole`; 160 of up to 6000 rows, D=128: 70
 //     us, 80 whole; but 184 of 6000 rows 109 and 93).  Not at D=128 where whole ones fill seven
 //     eighths or more of the 512 places (448 of 4500 rows: 175 us in parts, 166 whole; 512 of 4096: 172
@@ -93,7 +95,7 @@ inline void dec_launch(DecGeom &g, int rows)
     g.single = P <= 64 ? 640 : P <= 256 ? 1024 : 384;
     g.fill = kCus * (kDecSlots / g.waves) * (128 / g.D) / P;
     g.part = g.D == 128 ? 2048 : 1024;
-    g.whole = P > 256 ? g.part : 1 << 30;
+    g.whole = P > 256 || (g.D == 64 && P > 128) ? g.part : 1 << 30;
     if (g.D == 128 && P > 128 && P <= 170) g.whole = 4096;
     if (g.D == 128 && P >= 448 && P <= 512) g.whole = 1 << 30;
     g.heads = g.D == 32 || P > 256 ? 8 : 1;
