@@ -45,8 +45,8 @@ struct DecGeom {
 //     136 of 9000 64 -> 60).  So do they where `fill` is one part for 129 to 170 problems, a
 //     third of the CUs or more idle, in long contexts (`whole`; 160 of up to 6000 rows, D=128: 70
 //     us, 80 whole; but 184 of 6000 rows 109 and 93).  Not at D=128 where whole ones fill seven
-//     eighths or more of the 512 places (448 of 4500 rows: 175 us in parts, 166 whole; 512 of 4096: 172
-//     and 165; 384 of 4500: 149 and 154).
+//     eighths or more of the 512 places (448 of 4500 rows: 175 us in parts, 166 whole; 512 of
+//     4096: 172 and 165; 384 of 4500: 149 and 154).
 constexpr int kDecSlots = 8;  // waves that a CU holds at D=128, each with a K and a V tile in LDS
 constexpr int kDecChunk = 256;
 __host__ __device__ inline int dec_splits(const DecGeom &g, int rows)
